@@ -54,18 +54,10 @@
 // grouped order of tile_of.
 #include <type_traits>
 
-#include "internal.h"
-
-#define PCM_LDS __attribute__((address_space(3)))
+#include "gemm_common.h"
 
 namespace pcm {
 namespace {
-
-// s_waitcnt immediates (gfx9 encoding: vmcnt[3:0]+[15:14], expcnt[6:4], lgkmcnt[11:8])
-constexpr int waitcnt_imm(int vm, int lgkm) {
-    return (vm & 0xF) | (7 << 4) | ((lgkm & 0xF) << 8) | (((vm >> 4) & 3) << 14);
-}
-constexpr int kNoVm = 63, kNoLgkm = 15;
 
 // Find this workgroup's group and row range. Returns false past the last tile.
 template <int BM>
@@ -134,18 +126,6 @@ __device__ inline bool tile_of(int64_t bid, int64_t grid, int64_t mt_upper, int 
     return true;
 }
 
-// Source row of A row r of the tile (rows past row1 repeat a valid row; their outputs are
-// never stored).
-__device__ inline int64_t a_source_row(const GemmArgs& g, int r, int row1) {
-    if (r >= row1) r = row1 - 1;
-    int64_t src = r;
-    if (g.gather) {
-        src = g.gather[r];
-        src = src < 0 ? 0 : (src >= g.a_rows ? g.a_rows - 1 : src);
-    }
-    return src;
-}
-
 // Weight row (element offset of its K = 0) of B row j of the tile; rows past N repeat row
 // N - 1 (their outputs are never stored).
 template <int MODE, int WTN, int OUT_COLS>
@@ -180,96 +160,6 @@ __device__ inline int b_source_col(const GemmArgs& g, int ntile, int j, bool* up
 // Raw buffer resource over `bytes` bytes at `base` (loads past the end read zero).
 __device__ inline __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-
-// Row of `a` (and of row_scale) behind output row r.
-__device__ inline int64_t scale_row(const GemmArgs& g, int r) {
-    if (!g.gather) return r;
-    const int64_t s = g.gather[r];
-    return s < 0 ? 0 : (s >= g.a_rows ? g.a_rows - 1 : s);
-}
-
-// SiLU(g) = g / (1 + e^-g) with the hardware reciprocal (about 1 ulp) instead of an IEEE
-// division; for g below about -88, e^-g is +inf and the result is -0.
-__device__ inline float silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
-
-// Shared epilogue: acc[nb][mb] holds C[row = .. + (lane & 15)][cols c0 .. c0+3].
-template <int MODE, int MB, int NBK, int WTM, int WTN, int OUT_COLS>
-__device__ inline void epilogue(const GemmArgs& g, const floatx4 (&acc)[NBK][MB], int row0,
-                                int row1, int ntile, int wm, int wn, int lane) {
-    const int N = g.N;
-    // The row scales of all of this lane's rows are loaded first, without branches, and
-    // waited for once, in code that every store follows. A scale load that is still in
-    // flight where the stores' branches (row and column bounds) merge makes the compiler
-    // wait for all outstanding memory operations before each store, the earlier stores
-    // included: the 64 stores of a wave then ran one after another (13 us of a 256 x 256
-    // projection tile).
-    float scs[MB];
-    if constexpr (MODE != kExpand) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int r = min(row0 + wm * WTM + mb * 16 + (lane & 15), row1 - 1);
-            scs[mb] = g.row_scale ? g.row_scale[scale_row(g, r)] : 1.0f;
-        }
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkm));
-    }
-    if constexpr (MODE == kExpand) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int r = row0 + wm * WTM + mb * 16 + (lane & 15);
-            if (r >= row1) continue;
-#pragma unroll
-            for (int nb = 0; nb < NBK / 2; ++nb) {
-                const int f = ntile * OUT_COLS + wn * (WTN / 2) + nb * 16 + (lane >> 4) * 4;
-                if (f >= N) continue;
-                const floatx4 gt = acc[nb][mb], up = acc[nb + NBK / 2][mb];
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = silu(gt[i]) * up[i];
-                *(float4*)((float*)g.out + (int64_t)r * N + f) = make_float4(v[0], v[1], v[2], v[3]);
-            }
-        }
-    } else if (base_mode(MODE) == kDownAccum && g.accumulate) {
-        // read-modify-write: each row block's values are loaded before its stores
-        float* O = (float*)g.out;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int r = row0 + wm * WTM + mb * 16 + (lane & 15);
-            if (r >= row1) continue;
-            float4 prev[NBK];
-#pragma unroll
-            for (int nb = 0; nb < NBK; ++nb) {
-                const int h = min(ntile * OUT_COLS + wn * WTN + nb * 16 + (lane >> 4) * 4, N - 4);
-                prev[nb] = *(const float4*)(O + (int64_t)r * N + h);
-            }
-            const float sc = scs[mb];
-#pragma unroll
-            for (int nb = 0; nb < NBK; ++nb) {
-                const int h = ntile * OUT_COLS + wn * WTN + nb * 16 + (lane >> 4) * 4;
-                if (h >= N) continue;
-                // the stored value plus the scaled product, each rounded (no fused multiply-add),
-                // so that accumulating adds exactly what the store path writes
-                *(float4*)(O + (int64_t)r * N + h) = make_float4(
-                    __fadd_rn(prev[nb].x, __fmul_rn(acc[nb][mb][0], sc)), __fadd_rn(prev[nb].y, __fmul_rn(acc[nb][mb][1], sc)),
-                    __fadd_rn(prev[nb].z, __fmul_rn(acc[nb][mb][2], sc)), __fadd_rn(prev[nb].w, __fmul_rn(acc[nb][mb][3], sc)));
-            }
-        }
-    } else {
-        float* O = (float*)g.out;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int r = row0 + wm * WTM + mb * 16 + (lane & 15);
-            if (r >= row1) continue;
-            const float sc = scs[mb];
-#pragma unroll
-            for (int nb = 0; nb < NBK; ++nb) {
-                const int h = ntile * OUT_COLS + wn * WTN + nb * 16 + (lane >> 4) * 4;
-                if (h >= N) continue;
-                *(float4*)(O + (int64_t)r * N + h) = make_float4(acc[nb][mb][0] * sc, acc[nb][mb][1] * sc,
-                                                                 acc[nb][mb][2] * sc, acc[nb][mb][3] * sc);
-            }
-        }
-    }
 }
 
 // bfloat16 -> float16, 8 lanes of a fragment (exact for |w| in float16's normal range)
@@ -717,140 +607,6 @@ __device__ bool il_item(const GemmArgs& g, int nt, int GN, int* s_item) {
                     s_item[4] = kslice;
                 }
                 start += cnt;
-            }
-        }
-    }
-    __syncthreads();
-    return s_item[5] != 0;
-}
-
-// Work item of workgroup bid in the expert-major order. Group x has m_x = ceil(rows / BM)
-// M-tiles; its m_x * nt items are walked in blocks of gn_x N-tiles (gn_x = window / m_x,
-// at least 1), the M-tile varying slowest within a block, so that the `window` workgroups
-// an XCD runs at once cover all of a group's rows for a few N-tiles: each weight tile is
-// fetched while every row block that needs it runs, each activation tile once per block.
-// Each XCD (bid % 8) takes a contiguous eighth of the list (every K slice, slice-major), or,
-// for groups of at least 16 N tiles in multiples of 8, every eighth window (below). A last
-// row block of at most TBM rows runs as the shorter tail tile.
-// Wave 0 counts and searches; the result is broadcast through LDS as for il_item.
-template <int BM, int TBM>
-__device__ bool em_item(const GemmArgs& g, int nt, int window, int* s_item) {
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int lo[4], cnt[4], m[4], local = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int x = lane * 4 + j;
-            int c = 0, b = 0;
-            if (g.offsets == nullptr) {
-                if (x == 0) c = (int)g.a_rows;
-            } else if (x < g.n) {
-                b = g.offsets[x];
-                c = g.offsets[x + 1] - b;
-            }
-            lo[j] = b;
-            cnt[j] = c;
-            m[j] = (c + BM - 1) / BM;
-            local += m[j] * nt;
-        }
-        const int x8 = (int)(blockIdx.x % 8), j8 = (int)(blockIdx.x / 8);
-        if (g.ksplit == 1 && nt % 8 == 0 && nt >= 16) {
-            // Window-interleaved assignment: a group's N tiles are cut into windows of gw tiles,
-            // gw the largest divisor of nt / 8 not above window / m (so that every window has
-            // the same width and their number is a multiple of 8), and window i runs on XCD
-            // i % 8. Every XCD then holds exactly an eighth of every group's items and works
-            // through the groups in step with the others (the same mix of tile shapes at the
-            // same time), instead of the XCDs holding different groups whose tiles take
-            // different times (Mixtral-shaped expansion -1.9%); within a window the M-tile
-            // varies slowest. With fewer than 16 N tiles a group's activation rows would be
-            // fetched by every XCD for one N tile each (OLMoE-shaped projection +5%), so the
-            // contiguous eighths below stay.
-            // A group whose last row block takes the tail tile walks its windows over the full
-            // row blocks first and then that row block over the same N tiles. Within an XCD the
-            // hardware deals workgroups to its four shader arrays in strict rotation, one
-            // array's turn waiting for a free compute unit there; with the tail row inside every
-            // window the tail tiles repeat with the window's period and, where that period is
-            // even, fall on the same one or two arrays, whose turns then come round faster than
-            // the others' (Mixtral-shaped expansion: per-workgroup timelines, all 70 tail tiles
-            // of an XCD on two of its arrays, 13% more work on the other two). A run of one
-            // group's tail tiles gives every array the same mix: the mean gap between two tiles
-            // on a compute unit fell from 4.8 to 1.1 us, the expansion 0.7% faster (its tiles
-            // run slower with the compute units fuller, the clock falling under the load).
-            const int n8 = nt / 8;
-            int gw[4], mf[4], xl = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int last = cnt[j] - (m[j] - 1) * BM;   // rows of the last row block
-                mf[j] = (m[j] > 0 && last <= TBM) ? m[j] - 1 : m[j];
-                const int lim = window / (mf[j] > 0 ? mf[j] : 1);
-                int d = lim < 1 ? 1 : (lim > n8 ? n8 : lim);
-                while (n8 % d != 0) --d;
-                gw[j] = d;
-                xl += m[j] * n8;
-            }
-            const int xincl = wave_incl_scan_i32(xl);
-            const bool valid = j8 < __builtin_amdgcn_readlane(xincl, 63);
-            if (lane == 0) s_item[5] = valid ? 1 : 0;
-            if (valid) {
-                int start = xincl - xl;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int items = m[j] * n8;
-                    if (j8 >= start && j8 < start + items) {
-                        const int q = j8 - start;
-                        int mm, col;
-                        if (q < mf[j] * n8) {              // the full row blocks, window by window
-                            const int gsize = gw[j] * mf[j];
-                            const int kw = q / gsize, in = q - kw * gsize;
-                            mm = in / gw[j];
-                            col = (kw * 8 + x8) * gw[j] + (in - mm * gw[j]);   // window kw * 8 + x8
-                        } else {                           // the tail row block, same N tiles
-                            const int t = q - mf[j] * n8;
-                            mm = m[j] - 1;
-                            col = ((t / gw[j]) * 8 + x8) * gw[j] + t % gw[j];
-                        }
-                        const int r0 = lo[j] + mm * BM;
-                        s_item[0] = lane * 4 + j;
-                        s_item[1] = r0;
-                        s_item[2] = min(lo[j] + cnt[j], r0 + BM);
-                        s_item[3] = col;
-                        s_item[4] = 0;
-                    }
-                    start += items;
-                }
-            }
-        } else {
-            const int incl = wave_incl_scan_i32(local);
-            // 32-bit arithmetic throughout: the host keeps item counts (times 8) within range
-            const int Tt = __builtin_amdgcn_readlane(incl, 63), TT = Tt * g.ksplit;
-            const int l0 = x8 * TT / 8, l1 = (x8 + 1) * TT / 8;
-            const bool valid = j8 < l1 - l0;
-            if (lane == 0) s_item[5] = valid ? 1 : 0;
-            if (valid) {
-                const int item = l0 + j8;
-                const int kslice = item / Tt;
-                const int id = item - kslice * Tt;
-                int start = incl - local;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int items = m[j] * nt;
-                    if (id >= start && id < start + items) {
-                        const int l = id - start;
-                        int gn = window / m[j];
-                        gn = gn < 1 ? 1 : (gn > nt ? nt : gn);
-                        const int gsize = gn * m[j];
-                        const int grp = l / gsize, in = l - grp * gsize;
-                        const int gcols = min(gn, nt - grp * gn);
-                        const int mm = in / gcols;
-                        const int r0 = lo[j] + mm * BM;
-                        s_item[0] = lane * 4 + j;
-                        s_item[1] = r0;
-                        s_item[2] = min(lo[j] + cnt[j], r0 + BM);
-                        s_item[3] = grp * gn + (in - mm * gcols);
-                        s_item[4] = kslice;
-                    }
-                    start += items;
-                }
             }
         }
     }

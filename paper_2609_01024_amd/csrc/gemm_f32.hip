@@ -1,142 +1,55 @@
-// Grouped float32 GEMMs for float32 layers (same operations as the bf16 kernels:
-// expansion with fused SwiGLU, down projection store or accumulate). Vector FMA with
-// LDS tiles of 64 rows x 64 weight rows x 16 K; each thread owns a 4 x 4 block. Small
-// float32 layers are bound by launch latency, not arithmetic.
-#include "internal.h"
+// Grouped float32 GEMMs for float32 layers (same operations as the bf16 kernels: expansion with
+// fused SwiGLU, down projection store or accumulate), on v_mfma_f32_16x16x4_f32: float32 operands,
+// products and sums.
+#include "gemm_ring.h"
 
 namespace pcm {
 namespace {
 
-constexpr int FBM = 64, FBN = 64, FBK = 16;
+struct ElemF32 {
+    static constexpr int SIZE = 4, NJ = 4;
+    using T = floatx4;
+    struct Silu {   // float32 layers: the library exponential and an IEEE division
+        __device__ static float silu(float g) { return g / (1.0f + expf(-g)); }
+    };
+    __device__ static T weights(const char* p) { return *(const T*)p; }
+    __device__ static T acts(const char* p) { return *(const T*)p; }
+    __device__ static floatx4 step(int j, const T& w, const T& a, floatx4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(w[j], a[j], c, 0, 0, 0);
+    }
+};
 
-__device__ bool find_tile_f32(const int32_t* __restrict__ offsets, int n, int64_t a_rows, int64_t mt,
-                              int* s_tile) {
-    if (offsets == nullptr) {
-        if (mt * FBM >= a_rows) return false;
-        s_tile[0] = 0;
-        s_tile[1] = (int)(mt * FBM);
-        s_tile[2] = (int)min<int64_t>(a_rows, (mt + 1) * FBM);
-        return true;
-    }
-    if (threadIdx.x == 0) {
-        s_tile[0] = -1;
-        int64_t start = 0;
-        for (int x = 0; x < n; ++x) {
-            const int b = offsets[x], c = (int)ceil_div(offsets[x + 1] - b, FBM);
-            if (mt >= start && mt < start + c) {
-                const int r0 = b + (int)(mt - start) * FBM;
-                s_tile[0] = x;
-                s_tile[1] = r0;
-                s_tile[2] = min(offsets[x + 1], r0 + FBM);
-                break;
-            }
-            start += c;
-        }
-    }
-    __syncthreads();
-    return s_tile[0] >= 0;
-}
+// 64 x 64 tiles (three workgroups on a compute unit, so one's epilogue and waits overlap the others'
+// MFMAs); 32 x 64 tiles where those would not fill the chip once. Both are bound by the MFMA rate
+// (154 TFLOP/s in a large dense product here) where tiles are many: 4000 tokens, 8 experts, top-2,
+// H 1024, F 2048: expansion 1051 -> 576 us (117 TFLOP/s), projection with mix and combine 552 ->
+// 353 us, against the vector-ALU tiles before. 64 x 128 and 128 x 128 tiles measured 0-5% and 3-40%
+// slower (fewer workgroups to overlap, a longer last round), a ring of two slices 2-8%.
+using WideF32 = RCfg<64, 64, 2, 2, 3>;
+using NarrowF32 = RCfg<32, 64, 2, 2, 4>;
 
 template <int MODE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int64_t mt_upper) {
-    __shared__ float As[FBK][FBM + 4];
-    __shared__ float Bs[FBK][FBN + 4];
-    __shared__ int s_tile[3];
-    const int64_t mt = blockIdx.x % mt_upper;
-    const int ntile = (int)(blockIdx.x / mt_upper);
-    if (!find_tile_f32(g.offsets, g.n, g.a_rows, mt, s_tile)) return;
-    const int e = s_tile[0], row0 = s_tile[1], row1 = s_tile[2];
-    const int tid = threadIdx.x, tm = tid / 16, tn = tid % 16;
-    const int K = g.K, N = g.N;
-    constexpr int kOutCols = (MODE == kExpand) ? FBN / 2 : FBN;
-
-    // staged element: row = tid / 4, k quad = tid % 4
-    const int lrow = tid / 4, kq = tid % 4;
-    const float* aptr = nullptr;
-    {
-        const int r = row0 + lrow;
-        if (r < row1) {
-            int64_t src = r;
-            if (g.gather) {
-                src = g.gather[r];
-                src = src < 0 ? 0 : (src >= g.a_rows ? g.a_rows - 1 : src);
-            }
-            aptr = (const float*)g.a + src * K + kq * 4;
-        }
-    }
-    const float* bptr = nullptr;
-    if (MODE == kExpand) {
-        const int half = lrow / (FBN / 2), f = ntile * kOutCols + lrow % (FBN / 2);
-        if (f < N) bptr = (const float*)(half ? g.b1 : g.b0) + ((int64_t)e * N + f) * K + kq * 4;
-    } else {
-        const int h = ntile * kOutCols + lrow;
-        if (h < N) bptr = (const float*)g.b0 + ((int64_t)e * N + h) * K + kq * 4;
-    }
-    int bcol[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        bcol[j] = (MODE == kExpand) ? (j < 2 ? tn * 2 + j : FBN / 2 + tn * 2 + j - 2) : tn * 4 + j;
-
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += FBK) {
-        const float4 av = aptr ? *(const float4*)(aptr + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 bv = bptr ? *(const float4*)(bptr + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-        As[kq * 4 + 0][lrow] = av.x; As[kq * 4 + 1][lrow] = av.y;
-        As[kq * 4 + 2][lrow] = av.z; As[kq * 4 + 3][lrow] = av.w;
-        Bs[kq * 4 + 0][lrow] = bv.x; Bs[kq * 4 + 1][lrow] = bv.y;
-        Bs[kq * 4 + 2][lrow] = bv.z; Bs[kq * 4 + 3][lrow] = bv.w;
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < FBK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][tm * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][bcol[j]];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + tm * 4 + i;
-        if (r >= row1) continue;
-        float* out = (float*)g.out + (int64_t)r * N;
-        if (MODE == kExpand) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int f = ntile * kOutCols + tn * 2 + j;
-                if (f < N) {
-                    const float gt = acc[i][j], up = acc[i][j + 2];
-                    out[f] = gt / (1.0f + expf(-gt)) * up;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int h = ntile * kOutCols + tn * 4 + j;
-                if (h < N) out[h] = (MODE == kDownAccum && g.accumulate) ? out[h] + acc[i][j] : acc[i][j];
-            }
-        }
-    }
+hipError_t launch_mode_f32(const GemmArgs& g, int64_t R, hipStream_t s) {
+    // expected tiles: full row blocks, and half a block of remainder for every group with rows.
+    // Below 768 (three on each of 256 compute units) the smaller tiles are faster: 32 rows over 32
+    // experts 25 against 46 us (projection, F 1024), 300 tokens over 8 experts 19 against 24 us;
+    // above, the larger ones: 777 tokens, 16 experts, top-4: 100 against 157 us (expansion, F 960).
+    const int64_t groups = g.offsets ? (R < g.n ? R : g.n) : 0;
+    const int64_t tiles = (R / 32 + groups + (g.offsets ? 0 : 1)) * ceil_div(g.N, MODE == kExpand ? 32 : 64) / 2;
+    return tiles >= 768 ? launch_ring<ElemF32, WideF32, MODE>(g, R, s, 1)
+                        : launch_ring<ElemF32, NarrowF32, MODE>(g, R, s, 1);
 }
 
 }  // namespace
 
-hipError_t launch_gemm_f32(GemmMode mode, const GemmArgs& g, int64_t R, hipStream_t s) {
-    const int64_t mt_upper = g.offsets ? ceil_div(R, FBM) + g.n : ceil_div(R, FBM);
-    const int out_cols = mode == kExpand ? FBN / 2 : FBN;
-    const int64_t grid = mt_upper * ceil_div(g.N, out_cols);
-    if (grid <= 0) return hipSuccess;
+hipError_t launch_gemm_f32(GemmMode mode, const GemmArgs& g0, int64_t R, hipStream_t s) {
+    GemmArgs g = g0;
+    g.ksplit = 1;
     switch (mode) {
-        case kExpand: gemm_f32_kernel<kExpand><<<(unsigned)grid, 256, 0, s>>>(g, mt_upper); break;
-        case kDownStore: gemm_f32_kernel<kDownStore><<<(unsigned)grid, 256, 0, s>>>(g, mt_upper); break;
-        default: gemm_f32_kernel<kDownAccum><<<(unsigned)grid, 256, 0, s>>>(g, mt_upper); break;
+        case kExpand: return launch_mode_f32<kExpand>(g, R, s);
+        case kDownStore: return launch_mode_f32<kDownStore>(g, R, s);
+        default: return launch_mode_f32<kDownAccum>(g, R, s);
     }
-    return hipGetLastError();
 }
 
 }  // namespace pcm
