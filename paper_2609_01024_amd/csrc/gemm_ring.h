@@ -20,46 +20,29 @@ struct RCfg {
     static constexpr int QA = BM / 8 / NW, LPW = QA + BN / 8 / NW;   // loads per wave and slice
     static constexpr int SA = BM * 128, SLICE = SA + BN * 128, LDS_BYTES = NS * SLICE;
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "every wave issues the same loads");
-    static_assert(WTM % 16 == 0 && WTN % 32 == 0, "whole MFMA blocks, gate/up halves");
+    static_assert(WTM % 16 == 0 && WTN % 16 == 0, "whole MFMA blocks");
     static_assert(NS >= 2 && (NS - 2) * LPW <= 62 && LDS_BYTES <= 160 * 1024, "vmcnt range, LDS");
 };
 
-// One tile: rows [row0, row1) of group e, N tile ntile. E: the element type (SIZE bytes, NJ MFMA
-// steps per chunk, weight and activation fragment reads, step<J>).
-template <class E, class C, int MODE>
-__device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
-                                          int ntile) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / C::WN, wn = wave % C::WN;
-    const int N = g.N;
-    const int64_t rowb = (int64_t)g.K * E::SIZE;   // bytes of a row of either operand
-    constexpr int kOutCols = (MODE == kExpand) ? C::BN / 2 : C::BN;
-    const int KT = g.K * E::SIZE / 128;
+// A workgroup barrier that neither the compiler's nor its scheduler's reordering crosses.
+__device__ __forceinline__ void ring_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 
-    // load q of a lane: row blk * 8 + lane / 8 of the slice's A or B part, 16-byte position
-    // lane % 8; every row index is loaded before any is used
-    const char* src[C::LPW];
-    int64_t srow[C::LPW];
-#pragma unroll
-    for (int q = 0; q < C::QA; ++q)
-        srow[q] = a_source_row(g, row0 + (q * C::NW + wave) * 8 + (lane >> 3), row1);
-#pragma unroll
-    for (int q = 0; q < C::LPW; ++q) {
-        const int lr = ((q < C::QA ? q : q - C::QA) * C::NW + wave) * 8 + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((lr >> 1) & 7);
-        const char* base;
-        if (q < C::QA) {
-            base = (const char*)g.a + srow[q] * rowb;
-        } else if (MODE == kExpand) {   // a wave's weight rows: half gate, half up of its columns
-            const int grp = lr / C::WTN, jj = lr % C::WTN, half = jj / (C::WTN / 2);
-            const int f = min(ntile * kOutCols + grp * (C::WTN / 2) + jj % (C::WTN / 2), N - 1);
-            base = (const char*)(half ? g.b1 : g.b0) + ((int64_t)e * N + f) * rowb;
-        } else {
-            base = (const char*)g.b0 + ((int64_t)e * N + min(ntile * kOutCols + lr, N - 1)) * rowb;
-        }
-        src[q] = base + chunk * 16;
-    }
+// The accumulators of one wave over KT slices (waves 0 .. C::NW - 1 of the workgroup). src[q]: this
+// lane's address of load q (A rows for q < QA, then B rows) in the first slice: row
+// (q' * NW + wave) * 8 + lane / 8 of its part, chunk (lane % 8) ^ ((row >> 1) & 7). KT barriers.
+// E: the element type (SIZE bytes, NJ MFMA steps per chunk, fragment reads, step).
+template <class E, class C>
+__device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, char* lds,
+                                          floatx4 (&acc)[C::NBK][C::MB]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / C::WN, wn = wave % C::WN;
     auto issue = [&](int slot) {
 #pragma unroll
         for (int q = 0; q < C::LPW; ++q) {
@@ -70,14 +53,11 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
             src[q] += 128;
         }
     };
-
-    floatx4 acc[C::NBK][C::MB];
 #pragma unroll
     for (int nb = 0; nb < C::NBK; ++nb)
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb) acc[nb][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int r16 = lane & 15, kg = lane >> 4;
-
 #pragma unroll
     for (int s = 0; s < C::NS - 1; ++s)
         if (s < KT) issue(s);
@@ -90,11 +70,7 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
             // every wave is done with slice kt - 1, whose slot takes slice kt + NS - 1
             if (kt + C::NS - 2 < KT) __builtin_amdgcn_s_waitcnt(waitcnt_imm((C::NS - 2) * C::LPW, 0));
             else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
+            ring_barrier();
             if (kt + C::NS - 1 < KT) issue((j + C::NS - 1) % C::NS);
             const char* S = lds + j * C::SLICE;
 #pragma unroll
@@ -115,8 +91,43 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
             }
         }
     }
-    epilogue<MODE, C::MB, C::NBK, C::WTM, C::WTN, kOutCols, typename E::Silu>(g, acc, row0, row1, ntile, wm,
-                                                                              wn, lane);
+}
+
+// One tile: rows [row0, row1) of group e, N tile ntile.
+template <class E, class C, int MODE>
+__device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
+                                          int ntile) {
+    static_assert(C::WTN % 32 == 0, "gate/up halves");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int N = g.N;
+    const int64_t rowb = (int64_t)g.K * E::SIZE;   // bytes of a row of either operand
+    constexpr int kOutCols = (MODE == kExpand) ? C::BN / 2 : C::BN;
+    const char* src[C::LPW];
+    int64_t srow[C::QA];   // every row index is loaded before any is used
+#pragma unroll
+    for (int q = 0; q < C::QA; ++q)
+        srow[q] = a_source_row(g, row0 + (q * C::NW + wave) * 8 + (lane >> 3), row1);
+#pragma unroll
+    for (int q = 0; q < C::LPW; ++q) {
+        const int lr = ((q < C::QA ? q : q - C::QA) * C::NW + wave) * 8 + (lane >> 3);
+        const int chunk = (lane & 7) ^ ((lr >> 1) & 7);
+        const char* base;
+        if (q < C::QA) {
+            base = (const char*)g.a + srow[q < C::QA ? q : 0] * rowb;
+        } else if (MODE == kExpand) {   // a wave's weight rows: half gate, half up of its columns
+            const int grp = lr / C::WTN, jj = lr % C::WTN, half = jj / (C::WTN / 2);
+            const int f = min(ntile * kOutCols + grp * (C::WTN / 2) + jj % (C::WTN / 2), N - 1);
+            base = (const char*)(half ? g.b1 : g.b0) + ((int64_t)e * N + f) * rowb;
+        } else {
+            base = (const char*)g.b0 + ((int64_t)e * N + min(ntile * kOutCols + lr, N - 1)) * rowb;
+        }
+        src[q] = base + chunk * 16;
+    }
+    floatx4 acc[C::NBK][C::MB];
+    ring_loop<E, C>(src, g.K * E::SIZE / 128, lds, acc);
+    epilogue<MODE, C::MB, C::NBK, C::WTM, C::WTN, kOutCols, typename E::Silu>(g, acc, row0, row1, ntile, wave / C::WN,
+                                                                              wave % C::WN, lane);
 }
 
 // Workgroups walk the expert-major order of em_item with the window `window`.

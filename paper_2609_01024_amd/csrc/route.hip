@@ -3,7 +3,7 @@
 // four logits as 64-bit keys (order-preserving float bits, then the complemented expert
 // id), so a wave-wide maximum picks the largest logit and, among equal logits, the lower
 // id. k rounds of the maximum give the slots in order.
-#include "internal.h"
+#include "gemm_ring.h"
 
 namespace pcm {
 
@@ -145,14 +145,10 @@ __device__ inline float bperm_f32(int at, float v) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(v)));
 }
 
-// One token by one wavefront (all 64 lanes active): writes its top-k ids and weights, path
-// bits and beta; returns its slot expert to lanes < k (0 elsewhere). mask_s: the packed mask
-// in LDS, ceil(n / 64) = EPL words per row; pl from path_lane(lane, k).
+// Top-k and softmax of one token by one wavefront (all 64 lanes active): lanes a < k get slot
+// a's expert and, in *weight, its weight (0 in both elsewhere). lv: expert lane + 64 q's logit.
 template <int EPL>
-__device__ inline int index_token(const float (&lv)[EPL], const uint64_t* mask_s, int n,
-                                  int k, int beta_mode, int64_t t, int lane, const PathLane& pl,
-                                  int32_t* ids, float* w, uint64_t* bits_out, float* beta_out) {
-    const int pa_ = pl.pa, pb_ = pl.pb;
+__device__ inline int select_token(const float (&lv)[EPL], int n, int k, int lane, float* weight) {
     uint64_t key[EPL];
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
@@ -217,7 +213,20 @@ __device__ inline int index_token(const float (&lv)[EPL], const uint64_t* mask_s
     float s = 0.0f;
     for (int a = 0; a < k; ++a) s += readlane_f32(ex, a);
     const int e = lane < k ? (int)(0xFFFFFFFFu - (uint32_t)mine) : 0;
-    const float p = lane < k ? ex / s : 0.0f;
+    *weight = lane < k ? ex / s : 0.0f;
+    return e;
+}
+
+// One token by one wavefront (all 64 lanes active): writes its top-k ids and weights, path
+// bits and beta; returns its slot expert to lanes < k (0 elsewhere). mask_s: the packed mask
+// in LDS, ceil(n / 64) = EPL words per row; pl from path_lane(lane, k).
+template <int EPL>
+__device__ inline int index_token(const float (&lv)[EPL], const uint64_t* mask_s, int n,
+                                  int k, int beta_mode, int64_t t, int lane, const PathLane& pl,
+                                  int32_t* ids, float* w, uint64_t* bits_out, float* beta_out) {
+    const int pa_ = pl.pa, pb_ = pl.pb;
+    float p;
+    const int e = select_token<EPL>(lv, n, k, lane, &p);
     if (lane < k) {
         int32_t* const ids_t = ids + t * k;  // scalar base, lane offset
         float* const w_t = w + t * k;
@@ -484,22 +493,106 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
 }
 
 // Router logits fused with the top-k (the router's own GEMM, Section 2: the scores the
-// router computes from h): logits[t, e] = x_t . W_r[e], float32 accumulation.
-// bf16, two launches:
-//  * router_part_kernel: every wave computes one 16-expert x 16-token block of partial dot
-//    products over one K slice on the matrix cores (v_mfma_f32_16x16x32_bf16, router rows
-//    as the first operand), fragments loaded straight from global memory; part[s][t][e];
-//  * router_topk_kernel: one wave per token sums the K slices in order (deterministic),
-//    writes the logits if asked, and runs the top-k on them.
-// The K split is chosen so that about 2048 waves share the work.
+// router computes from h): logits[t, e] = x_t . W_r[e], float32 accumulation, on the matrix
+// cores (v_mfma_f32_16x16x32_bf16, router rows as the first operand). The sums over K slices
+// run in a fixed order (deterministic). Two forms (launch_router has the rule):
+//  * router_fused_kernel, one launch: a workgroup owns 32 tokens and every expert. Its first waves run the ring of gemm_ring.h over the 128-byte K slices of the tokens'
+//    and the experts' rows (4 to 12 slices in LDS, so that most of a compute unit's 64 bytes per
+//    clock stay requested), the logits go through LDS, and sixteen waves run the top-k of two
+//    tokens each. x is read once; the router weights come from L2. 8192 tokens, H 2048, 64
+//    experts: 39.0 -> 13.4 us; 16384 tokens, H 7168, 256 experts: 830 -> 158 us.
+//  * router_part_kernel, then router_topk_kernel: a workgroup computes one 16-expert x 16-token
+//    block over one K slice, its four waves splitting the slice and adding through LDS;
+//    part[s][t][e]. Then one wave per token adds the slices, all loaded at once, and runs the
+//    top-k. A few tokens then still use many compute units. (24 tokens, H 2048, 64 experts: 9.4 ->
+//    6.0 us; with a wave per K slice, the top-k kernel added up to 64 slices in eight rounds of
+//    loads.)
+constexpr int kRouterTok = 32, kRouterSlices = 16;
+
+struct ElemRouter {   // bf16 x bf16, the router rows as the first operand
+    static constexpr int SIZE = 2, NJ = 1;
+    using T = bf16x8;
+    __device__ static T weights(const char* p) { return *(const T*)p; }
+    __device__ static T acts(const char* p) { return *(const T*)p; }
+    __device__ static floatx4 step(int, const T& w, const T& a, floatx4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, c, 0, 0, 0);
+    }
+};
+
+template <class C>
+__device__ __forceinline__ void router_fused_body(char* lds, const uint16_t* __restrict__ x,
+                                                  const uint16_t* __restrict__ wr, int64_t T, int H,
+                                                  int n, int k, float* __restrict__ logits,
+                                                  int32_t* __restrict__ ids, float* __restrict__ w) {
+    constexpr int EPL = C::BN / 64;
+    constexpr int ROW = EPL * 64 + 4;   // floats of a padded LDS row of logits
+    static_assert(C::BM == kRouterTok && kRouterTok * ROW * 4 <= C::LDS_BYTES, "logits in the ring's LDS");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t t0 = (int64_t)blockIdx.x * kRouterTok;
+    const int KT = H / 64;
+    floatx4 acc[C::NBK][C::MB];
+    if (wave < C::NW) {   // wave-uniform
+        const char* src[C::LPW];
+#pragma unroll
+        for (int q = 0; q < C::LPW; ++q) {
+            const int lr = ((q < C::QA ? q : q - C::QA) * C::NW + wave) * 8 + (lane >> 3);
+            const int64_t row = q < C::QA ? min<int64_t>(t0 + lr, T - 1) : min(lr, n - 1);
+            src[q] = (const char*)((q < C::QA ? x : wr) + row * H) + ((lane & 7) ^ ((lr >> 1) & 7)) * 16;
+        }
+        ring_loop<ElemRouter, C>(src, KT, lds, acc);
+    } else {
+        for (int kt = 0; kt < KT; ++kt) ring_barrier();   // the loop's barriers
+    }
+    __syncthreads();   // the last slice has been read
+    float* const lg = (float*)lds;
+    if (wave < C::NW) {   // acc[nb][mb][i]: token .. + (lane & 15), expert .. + 4 * (lane >> 4) + i
+        const int wm = wave / C::WN, wn = wave % C::WN;
+#pragma unroll
+        for (int nb = 0; nb < C::NBK; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb)
+                *(floatx4*)(lg + (wm * C::WTM + mb * 16 + (lane & 15)) * ROW + wn * C::WTN + nb * 16 + 4 * (lane >> 4)) = acc[nb][mb];
+    }
+    __syncthreads();
+    for (int tib = wave; tib < kRouterTok; tib += 16) {
+        const int64_t t = t0 + tib;
+        if (t >= T) return;   // wave-uniform; no barrier follows
+        float lv[EPL];
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) {
+            const int e = lane + 64 * q;
+            lv[q] = e < n ? lg[tib * ROW + e] : 0.0f;
+            if (logits && e < n) logits[t * n + e] = lv[q];
+        }
+        float p;
+        const int e = select_token<EPL>(lv, n, k, lane, &p);
+        if (lane < k) {
+            ids[t * k + lane] = e;
+            w[t * k + lane] = p;
+        }
+    }
+}
+
+// (a device function of its own: the host pass emits no kernel whose body loads into LDS)
+template <class C>
+__global__ __launch_bounds__(1024) void router_fused_kernel(const uint16_t* __restrict__ x,
+                                                            const uint16_t* __restrict__ wr,
+                                                            int64_t T, int H, int n, int k,
+                                                            float* __restrict__ logits,
+                                                            int32_t* __restrict__ ids,
+                                                            float* __restrict__ w) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    router_fused_body<C>(lds, x, wr, T, H, n, k, logits, ids, w);
+}
+
 __global__ __launch_bounds__(256) void router_part_kernel(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ wr,
                                                           int64_t T, int H, int n, int et,
-                                                          int64_t tt, int ks, int steps,
+                                                          int64_t tt, int steps,
                                                           float* __restrict__ part) {
-    const int lane = threadIdx.x & 63;
-    const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (unit >= (int64_t)et * tt * ks) return;  // wave-uniform
+    __shared__ floatx4 red[3][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t unit = blockIdx.x;
     const int e_tile = (int)(unit % et);
     const int64_t t_tile = (unit / et) % tt;
     const int s = (int)(unit / ((int64_t)et * tt));
@@ -507,75 +600,52 @@ __global__ __launch_bounds__(256) void router_part_kernel(const uint16_t* __rest
     const int64_t t0 = t_tile * 16;
     const int64_t tok = t0 + r16 < T ? t0 + r16 : T - 1;
     const int e = e_tile * 16 + r16 < n ? e_tile * 16 + r16 : n - 1;
-    const int KT = H / 32, k0 = s * steps, k1 = k0 + steps < KT ? k0 + steps : KT;
+    const int KT = H / 32, k0 = (s * 4 + wave) * steps, k1 = k0 + steps < KT ? k0 + steps : KT;
     const bf16x8* xp = (const bf16x8*)(x + tok * H + kg * 8);
     const bf16x8* wp = (const bf16x8*)(wr + (int64_t)e * H + kg * 8);
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
     for (int kt = k0; kt < k1; ++kt)
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[kt * 4], xp[kt * 4], acc, 0, 0, 0);
+    if (wave) red[wave - 1][lane] = acc;
+    __syncthreads();
+    if (wave) return;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) acc += red[q][lane];
     // acc[r]: expert e_tile*16 + 4*kg + r of token t0 + r16
     const int npad = et * 16;
-    if (t0 + r16 < T) {
-        float* dst = part + ((int64_t)s * T + t0 + r16) * npad + e_tile * 16 + 4 * kg;
-        *(float4*)dst = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    }
+    if (t0 + r16 < T)
+        *(floatx4*)(part + ((int64_t)s * T + t0 + r16) * npad + e_tile * 16 + 4 * kg) = acc;
 }
 
 template <int EPL>
-__global__ __launch_bounds__(256) void router_topk_kernel(const float* __restrict__ part,
-                                                          int64_t T, int n, int npad, int ks,
-                                                          int k, float* __restrict__ logits,
-                                                          int32_t* __restrict__ ids,
-                                                          float* __restrict__ w) {
-    __shared__ float lg[4][kMaxN];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t t = (int64_t)blockIdx.x * 4 + wave;
-    if (t >= T) return;  // wave-uniform; only wave-local LDS use follows
-#pragma unroll
-    for (int j = 0; j < EPL; ++j) {
-        const int e = lane + 64 * j;
-        if (e >= n) continue;
-        float v = 0.0f;
-        for (int s = 0; s < ks; ++s) v += part[((int64_t)s * T + t) * npad + e];
-        lg[wave][e] = v;
-        if (logits) logits[t * n + e] = v;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    route_token<EPL>(lg[wave], n, k, lane, ids + t * k, w + t * k);
-}
-
-// The same for many K slices (large H, few tokens): one workgroup per token, thread e
-// sums expert e's slices (independent loads, several in flight), then wave 0 runs the
-// top-k. The sum over slices runs in the same order as in router_topk_kernel.
-template <int EPL>
-__global__ __launch_bounds__(256) void router_topk_wide_kernel(const float* __restrict__ part,
-                                                               int64_t T, int n, int npad, int ks,
-                                                               int k, float* __restrict__ logits,
-                                                               int32_t* __restrict__ ids,
-                                                               float* __restrict__ w) {
-    __shared__ float lg[kMaxN];
+__global__ __launch_bounds__(64) void router_topk_kernel(const float* __restrict__ part, int64_t T,
+                                                         int n, int npad, int ks, int k,
+                                                         float* __restrict__ logits,
+                                                         int32_t* __restrict__ ids,
+                                                         float* __restrict__ w) {
+    const int lane = threadIdx.x;
     const int64_t t = blockIdx.x;
-    for (int e = threadIdx.x; e < n; e += blockDim.x) {
-        const float* p = part + t * npad + e;
-        const int64_t stride = T * npad;
-        float v = 0.0f;
-        int s = 0;
-        for (; s + 8 <= ks; s += 8) {
-            float q[8];
+    float v[EPL][kRouterSlices];   // every slice loaded before the first sum
 #pragma unroll
-            for (int j = 0; j < 8; ++j) q[j] = p[(s + j) * stride];
+    for (int q = 0; q < EPL; ++q)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v += q[j];
-        }
-        for (; s < ks; ++s) v += p[s * stride];
-        lg[e] = v;
-        if (logits) logits[t * n + e] = v;
+        for (int s = 0; s < kRouterSlices; ++s)
+            v[q][s] = (s < ks && lane + 64 * q < npad) ? part[((int64_t)s * T + t) * npad + lane + 64 * q] : 0.0f;
+    float lv[EPL];
+#pragma unroll
+    for (int q = 0; q < EPL; ++q) {
+        lv[q] = v[q][0];
+#pragma unroll
+        for (int s = 1; s < kRouterSlices; ++s) lv[q] += v[q][s];
+        if (logits && lane + 64 * q < n) logits[t * n + lane + 64 * q] = lv[q];
     }
-    __syncthreads();
-    if (threadIdx.x < 64) route_token<EPL>(lg, n, k, threadIdx.x, ids + t * k, w + t * k);
+    float p;
+    const int e = select_token<EPL>(lv, n, k, lane, &p);
+    if (lane < k) {
+        ids[t * k + lane] = e;
+        w[t * k + lane] = p;
+    }
 }
 
 // float32: one wavefront per token; lane e (+64 j) forms x_t . W_r[e] with h ascending.
@@ -667,22 +737,50 @@ hipError_t launch_route_paths(const float* logits, const uint64_t* packed, int64
     return hipGetLastError();
 }
 
-// K split of the router GEMM: slices of `steps` 32-wide K steps, about 2048 waves in all.
+// K split of the two-launch router: ks slices of 4 x `steps` 32-wide K steps (a wave's share),
+// about 512 workgroups in all.
 void router_split(int64_t T, int H, int n, int* et, int64_t* tt, int* ks, int* steps) {
     *et = (int)ceil_div(n, 16);
     *tt = ceil_div(T, 16);
     const int KT = H / 32;
-    int64_t want = ceil_div(2048, (int64_t)*et * *tt);
-    want = want < 1 ? 1 : (want > KT ? KT : want);
-    *steps = (int)ceil_div(KT, want);
-    *ks = (int)ceil_div(KT, *steps);
+    int64_t want = 512 / ((int64_t)*et * *tt);
+    want = want < 1 ? 1 : (want > kRouterSlices ? kRouterSlices : want);
+    *steps = (int)ceil_div(KT, want * 4);
+    *ks = (int)ceil_div(KT, *steps * 4);
 }
 
+// Sized for slices of the K steps that about 2048 waves leave each (never fewer than router_split's).
 size_t router_ws_bytes(int64_t T, int H, int n) {
-    int et, ks, steps;
-    int64_t tt;
-    router_split(T, H, n, &et, &tt, &ks, &steps);
+    const int64_t et = ceil_div(n, 16), tt = ceil_div(T, 16), KT = H / 32;
+    int64_t want = ceil_div(2048, et * tt > 0 ? et * tt : 1);
+    want = want < 1 ? 1 : (want > KT ? KT : want);
+    const int64_t ks = ceil_div(KT, ceil_div(KT, want));
     return align_up((size_t)ks * T * et * 16 * sizeof(float), 256);
+}
+
+template <class C>
+hipError_t launch_router_fused(const uint16_t* x, const uint16_t* wr, int64_t T, int H, int n, int k,
+                               float* logits, int32_t* ids, float* w, hipStream_t s) {
+    // set on every launch (idempotent, and the library keeps no state between calls)
+    const hipError_t err = hipFuncSetAttribute((const void*)router_fused_kernel<C>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+    if (err != hipSuccess) return err;
+    router_fused_kernel<C><<<(unsigned)ceil_div(T, kRouterTok), 1024, C::LDS_BYTES, s>>>(x, wr, T, H, n, k, logits,
+                                                                                        ids, w);
+    return hipGetLastError();
+}
+
+// Whether the one-launch router is the faster one. Its workgroups take the bytes of 32 tokens and
+// of every expert (in 64s) at about 65 GB/s each, one workgroup on each of 256 compute units at a
+// time; the two launches move 32 rows per 16 x 16 block at about 9 TB/s in all, 138 times as much
+// (both with 5-6 us besides; H 2048, 64 experts: 1024 tokens 11.2 against 9.4 us, 2048 tokens 11.5
+// against 13.4, 8192 tokens 13.4 against 36.6; H 7168, 256 experts: 1024 tokens 65.6 against 56.4,
+// 2048 tokens 65.9 against 105). With at most 32 experts half of its expert rows would be padding
+// (8 experts, H 4096, 8192 tokens: 21.3 against 19.4 us).
+bool router_fused(int64_t T, int H, int n) {
+    if (n <= 32) return false;
+    const int64_t row = (int64_t)H * 2, rounds = ceil_div(ceil_div(T, kRouterTok), 256);
+    return rounds * (kRouterTok + ceil_div(n, 64) * 64) * row * 138 < ceil_div(T, 16) * ceil_div(n, 16) * 32 * row;
 }
 
 hipError_t launch_router(bool bf16, const void* x, const void* wr, int64_t T, int H, int n, int k,
@@ -693,29 +791,27 @@ hipError_t launch_router(bool bf16, const void* x, const void* wr, int64_t T, in
                                                                   T, H, n, k, logits, ids, w);
         return hipGetLastError();
     }
+    const uint16_t *xb = (const uint16_t*)x, *wb = (const uint16_t*)wr;
+    const int epl = (int)ceil_div(n, 64);
+    if (router_fused(T, H, n)) {
+        switch (epl) {
+            case 1: return launch_router_fused<RCfg<32, 64, 2, 2, 12>>(xb, wb, T, H, n, k, logits, ids, w, s);
+            case 2: return launch_router_fused<RCfg<32, 128, 2, 2, 7>>(xb, wb, T, H, n, k, logits, ids, w, s);
+            case 3: return launch_router_fused<RCfg<32, 192, 2, 2, 5>>(xb, wb, T, H, n, k, logits, ids, w, s);
+            default: return launch_router_fused<RCfg<32, 256, 2, 2, 4>>(xb, wb, T, H, n, k, logits, ids, w, s);
+        }
+    }
     int et, ks, steps;
     int64_t tt;
     router_split(T, H, n, &et, &tt, &ks, &steps);
-    const int64_t units = (int64_t)et * tt * ks;
-    router_part_kernel<<<(unsigned)ceil_div(units, 4), 256, 0, s>>>(
-        (const uint16_t*)x, (const uint16_t*)wr, T, H, n, et, tt, ks, steps, part);
-    const dim3 grid((unsigned)ceil_div(T, 4)), block(256);
+    router_part_kernel<<<(unsigned)(et * tt * ks), 256, 0, s>>>(xb, wb, T, H, n, et, tt, steps, part);
     const int npad = et * 16;
-    if (ks * ceil_div(n, 64) > 16) {   // long serial sums per lane: spread them over a workgroup
-        const dim3 wgrid((unsigned)T);
-        switch (ceil_div(n, 64)) {
-            case 1: router_topk_wide_kernel<1><<<wgrid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-            case 2: router_topk_wide_kernel<2><<<wgrid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-            case 3: router_topk_wide_kernel<3><<<wgrid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-            default: router_topk_wide_kernel<4><<<wgrid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        }
-        return hipGetLastError();
-    }
-    switch (ceil_div(n, 64)) {
-        case 1: router_topk_kernel<1><<<grid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        case 2: router_topk_kernel<2><<<grid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        case 3: router_topk_kernel<3><<<grid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        default: router_topk_kernel<4><<<grid, block, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
+    const unsigned grid = (unsigned)T;
+    switch (epl) {
+        case 1: router_topk_kernel<1><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
+        case 2: router_topk_kernel<2><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
+        case 3: router_topk_kernel<3><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
+        default: router_topk_kernel<4><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
     }
     return hipGetLastError();
 }

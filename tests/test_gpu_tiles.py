@@ -43,3 +43,18 @@ def test_f32_dense_swiglu_accumulate(T):
     torch.cuda.synchronize()
     assert_y_close(y0.cpu().numpy(), oracle.dense_swiglu(inp.x, inp.s_gate, inp.s_up, inp.s_down), "f32", cfg.name)
     assert torch.equal(y, base + y0)
+
+
+# router GEMM: one launch (32-token workgroups, all experts) or two (16 x 16 blocks, K slices);
+# token and expert remainders, every count of 64-expert groups, one 64-wide K slice, and tokens on
+# both sides of the line between the two forms
+@pytest.mark.parametrize("T,H,n,k", [(2048, 2048, 64, 8), (1024, 2048, 64, 8), (4129, 64, 33, 3),
+                                     (5001, 192, 100, 8), (4097, 832, 130, 5), (3001, 1024, 256, 8),
+                                     (17, 7168, 256, 8), (5, 64, 1, 1), (1, 4096, 8, 2)])
+def test_router_forms(T, H, n, k):
+    from test_gpu_parity import check_route_logits
+    say(f"router T={T} H={H} n={n}")
+    g = torch.Generator().manual_seed(T + n)
+    x = torch.randn((T, H), generator=g).to(torch.bfloat16)
+    wr = (torch.randn((n, H), generator=g) * 0.02).to(torch.bfloat16)
+    check_route_logits(x, wr, k, f"T={T} H={H} n={n} k={k}")
