@@ -312,11 +312,13 @@ pcm_status pcm_project_combine_scored(pcm_dtype dtype, const void* u, const void
 /* ---------------------------------------------------------------- tests and measurement
  * A layer never needs these. The *_tuned calls are the calls above with a pcm_tuning that
  * forces kernel choices the library otherwise makes by shape (every choice computes the same
- * bits) and that records HIP events between the internal stages of a call; tuning = NULL is
- * the plain call. They let tests check each kernel on the same inputs and let benchmarks time
+ * bits, but for the splits of K: the large tiles' projection slices, and the streaming kernel's
+ * default ring, which adds four partial sums where rows are few and K is long) and that records
+ * HIP events between the internal stages of a call; tuning = NULL is the plain call. They let tests check each kernel on the same inputs and let benchmarks time
  * each stage on the stream it runs on. Values outside the documented sets give PCM_ERR_ARG. */
 typedef struct pcm_tuning {
-    int tile;              /* 0: chosen by the mean rows per expert; 'S' the few-row streaming
+    int tile;              /* 0: chosen by the shape (smaller tiles of 64 rows among the choices);
+                              'S' the few-row streaming
                               kernel, 'M' the medium tiles, 'L' the large tiles on four waves,
                               'W' the large tiles on eight waves (two per SIMD; the default
                               for an expansion that takes the large tiles); for 'L' and 'W'
@@ -327,7 +329,7 @@ typedef struct pcm_tuning {
     int order_down;        /* the same for projection GEMMs */
     int em_window;         /* workgroups per expert-major window (0: 8) */
     int group_n;           /* N tiles per group of the grouped order (0: 4) */
-    int stream_depth;      /* streaming kernel: -1 by GEMM side; 0 the register-ring kernel;
+    int stream_depth;      /* streaming kernel: -1 by shape; 0 the register-ring kernel;
                               2, 3, 4 or 6 LDS ring slots */
     void* stage_events[4]; /* hipEvent_t each, or NULL: the project-and-combine calls record
                               them on `stream` before the mix, before the projection GEMM,

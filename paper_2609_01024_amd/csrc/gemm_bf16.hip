@@ -13,7 +13,7 @@
 // Both operands are K-contiguous (x rows and W rows run along H; Z rows and W_down rows
 // along F), so a lane's 8 consecutive K values of a row are one 16-byte load.
 //
-// Three kernel shapes share the epilogue and the work decomposition:
+// Four kernel shapes share the epilogue and the work decomposition (pick_tile, pick_shape):
 //  * "interleaved" (large tiles, 256 x 256): four waves, one per SIMD, each owning a 128 x 128
 //    block of C in 256 accumulation registers, or eight waves, two per SIMD, each owning a
 //    128 x 64 block in 128 (the expansion's default: while one wave of a SIMD waits, the other
@@ -37,7 +37,10 @@
 //    and its activation block through a ring of its own in LDS (no barrier), every direct
 //    load covering whole 128-byte lines; the weights are the traffic. A register-ring
 //    variant (fragments loaded straight into registers several k-steps ahead) runs where
-//    the ring's 32-bit offsets would not reach.
+//    the ring's 32-bit offsets would not reach. Where K is long, the four waves of a workgroup
+//    split it over the same weight rows (LStream).
+//  * "ring" (gemm_ring.h: 64 x 128 and 64 x 64 tiles, several workgroups on a compute unit): few
+//    rows per group, and products whose large tiles would leave most of the chip idle.
 // The MFMA takes the weight fragment as its first operand, so each lane's four
 // accumulators are four consecutive output columns of one row (16-byte stores). For the
 // expansion, a wave's weight rows are half gate and half up for the same columns, so the
@@ -54,7 +57,7 @@
 // grouped order of tile_of.
 #include <type_traits>
 
-#include "gemm_common.h"
+#include "gemm_ring.h"
 
 namespace pcm {
 namespace {
@@ -163,7 +166,7 @@ __device__ inline __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t 
 }
 
 // bfloat16 -> float16, 8 lanes of a fragment (exact for |w| in float16's normal range)
-__device__ inline halfx8 widen_to_f16(const bf16x8& v) {
+__device__ inline halfx8 widen_to_f16(bf16x8 v) {
     const uint4 q = __builtin_bit_cast(uint4, v);
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
     halfx8 h;
@@ -181,12 +184,15 @@ template <int MODE>
 struct Frag {
     using T = typename std::conditional<MODE == kExpand, bf16x8, halfx8>::type;
     // a weight fragment as loaded (8 bf16 values, or 8 float16 values for half_weights)
-    __device__ static T wide(const bf16x8& v) {
+    __device__ static T wide(bf16x8 v) {
         if constexpr (MODE == kExpand) return v;
         else if constexpr (half_weights(MODE)) return __builtin_bit_cast(halfx8, v);
         else return widen_to_f16(v);
     }
-    __device__ static T weights(const char* p) { return wide(*(const bf16x8*)p); }
+    __device__ static T weights(const char* p) {
+        const bf16x8 v = *(const bf16x8*)p;
+        return wide(v);
+    }
     __device__ static T acts(const char* p) { return *(const T*)p; }
 };
 __device__ inline floatx4 mfma_step(const bf16x8& w, const bf16x8& a, floatx4 c) {
@@ -641,7 +647,7 @@ __global__ __launch_bounds__(C::NT) void gemm_il_kernel(GemmArgs g, int64_t mt_u
             return;
         }
     } else if (order == kExpertMajor) {
-        if (!em_item<C::BM, CT::BM>(g, nt, group_n, s_item)) return;
+        if (!em_item<C::BM, CT::BM>(g, nt, group_n, true, s_item)) return;
         e = s_item[0], row0 = s_item[1], row1 = s_item[2], ntile = s_item[3], kslice = s_item[4];
         __syncthreads();
     } else {
@@ -881,27 +887,77 @@ __global__ __launch_bounds__(SWAVES * 64) void gemm_stream_kernel(GemmArgs g, in
 // layout puts four lanes on a row), half a cache line per row, and the weight stream then ran
 // at 5.4 TB/s; here each direct buffer -> LDS load covers 8 rows x 128 bytes (the 64 K values
 // of two MFMA steps, whole lines) and the MFMA fragments are read back from LDS. Ring slot j of
-// a wave holds NB blocks of 16 weight rows and one block of the 16 activation rows, each row
+// a wave holds NB blocks of 16 weight rows and MB blocks of 16 activation rows, each row
 // 128 bytes with chunk c of row r at position c ^ ((r >> 1) & 7) (conflict-free fragment
-// reads); D slots, D - 1 pairs in flight. No barrier: each wave owns its ring, and a slot is
-// reloaded only after the MFMAs that used its fragments. With the activations in the ring as
-// well, the loop holds no load into registers, whose waits the compiler would place itself
+// reads); D slots, D - 1 slices in flight. No barrier in the loop: each wave owns its ring, and a
+// slot is reloaded only after the MFMAs that used its fragments. With the activations in the ring
+// as well, the loop holds no load into registers, whose waits the compiler would place itself
 // (it drained every load in flight at the loop head). K is a multiple of 64 (as the layer
 // entry points require of H and F), and `a` and one group's weights are below 4 GiB (32-bit
 // buffer offsets); otherwise the register-ring kernel runs.
+//
+// KW = 1: the four waves own NB * 16 weight rows each. KW = 4: they own the same NB * 16 rows and
+// take every fourth slice of K, adding their sums through LDS in wave order: four times the
+// workgroups where the weight rows alone would leave compute units idle or too little in flight.
 // (The body is a device function: the buffer resources and LDS-destination loads it uses have
 // no host form, and the host pass does not emit a kernel whose own body uses them.)
-template <int MODE, int NB, int D>
+template <int MODE, int NB, int MB, int D, int KW>
+struct LStream {
+    static constexpr int kWaveCols = (MODE == kExpand) ? NB * 8 : NB * 16;   // output columns
+    static constexpr int kWgCols = kWaveCols * (KW == 1 ? SWAVES : 1);
+    static constexpr int kSlot = (NB + MB) * 2048;   // NB weight blocks, then MB activation blocks
+    static constexpr int kLds = SWAVES * D * kSlot;
+    static constexpr int kLoads = 2 * (NB + MB);     // loads of a slice
+    static_assert(KW == 1 || KW == SWAVES, "the waves share their rows or their slices");
+    static_assert((MODE != kExpand || NB % 2 == 0) && D >= 2 && (D - 1) * kLoads <= 62, "gate/up halves; vmcnt range");
+    static_assert(KW == 1 || SWAVES * NB * MB * 1024 <= kLds, "the waves' sums fit the ring");
+};
+
+// One output row r and 4 columns from c on: the projection's store or accumulation.
+template <int MODE>
+__device__ inline void store_down4(const GemmArgs& g, int r, int c, const floatx4& acc, float sc) {
+    float4 v = make_float4(acc[0] * sc, acc[1] * sc, acc[2] * sc, acc[3] * sc);
+    float4* dst = (float4*)((float*)g.out + (int64_t)r * g.N + c);
+    if (base_mode(MODE) == kDownAccum && g.accumulate) {
+        const float4 o = *dst;
+        v.x = __fadd_rn(o.x, v.x); v.y = __fadd_rn(o.y, v.y);
+        v.z = __fadd_rn(o.z, v.z); v.w = __fadd_rn(o.w, v.w);
+    }
+    *dst = v;
+}
+__device__ inline void store_swiglu4(const GemmArgs& g, int r, int c, const floatx4& gate, const floatx4& up) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = silu(gate[i]) * up[i];
+    *(float4*)((float*)g.out + (int64_t)r * g.N + c) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// Rows [row0, row1) of group e (at most 16 * MB), N tile ntile.
+template <int MODE, int NB, int MB, int D, int KW>
 __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
                                              int ntile) {
-    static_assert(NB % 2 == 0 && D >= 2 && (D - 1) * (2 * NB + 2) <= 63, "gate/up halves; vmcnt range");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    using C = LStream<MODE, NB, MB, D, KW>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int K = g.K, N = g.N;
-    constexpr int kWaveCols = (MODE == kExpand) ? NB * 8 : NB * 16;
-    const int col0 = (ntile * SWAVES + wave) * kWaveCols;
-    if (col0 >= N) return;  // wave-uniform; no barrier follows
-    constexpr int kSlot = (NB + 1) * 2048;   // NB weight blocks, then the activation block
-    char* ring = lds + wave * (D * kSlot);
+    const int col0 = KW == 1 ? (ntile * SWAVES + wave) * C::kWaveCols : ntile * C::kWaveCols;
+    if (KW == 1 && col0 >= N) return;  // wave-uniform; no barrier follows
+    char* ring = lds + wave * (D * C::kSlot);
+    const int r16 = lane & 15, kg = lane >> 4;
+    // source rows of the activation loads, (the projection) the row scales: loaded first, and used
+    // only once the first weights are on their way too
+    int arow[MB][2];
+    float sc[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            arow[m][h] = min(row0 + m * 16 + h * 8 + (lane >> 3), row1 - 1);
+            if (g.gather) arow[m][h] = g.gather[arow[m][h]];
+        }
+        sc[m] = 1.0f;
+        if constexpr (MODE != kExpand)
+            if (g.row_scale) sc[m] = g.row_scale[scale_row(g, min(row0 + m * 16 + r16, row1 - 1))];
+    }
     // weight row (within expert e) behind row R of block b; rows past N repeat row N - 1
     auto wrow = [&](int b, int R) {
         const int wr = (MODE == kExpand) ? col0 + (b % (NB / 2)) * 16 + R : col0 + b * 16 + R;
@@ -911,148 +967,183 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
     const __amdgpu_buffer_rsrc_t rb0 = buffer_rsrc((const char*)g.b0 + e * wbytes, (uint32_t)wbytes);
     const __amdgpu_buffer_rsrc_t rb1 =
         MODE == kExpand ? buffer_rsrc((const char*)g.b1 + e * wbytes, (uint32_t)wbytes) : rb0;
-    // load (b, h) of a pair: rows h * 8 + lane / 8 of block b, position lane % 8
-    uint32_t voff[NB][2];
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(g.a, (uint32_t)((int64_t)g.a_rows * K * 2));
+    // load (b, h) of a slice: rows h * 8 + lane / 8 of block b, position lane % 8
+    uint32_t voff[NB][2], aoff[MB][2];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int R = h * 8 + (lane >> 3);
-            const int chunk = (lane & 7) ^ ((R >> 1) & 7);
-            voff[b][h] = (uint32_t)(wrow(b, R) * (int64_t)K * 2 + chunk * 16);
+            voff[b][h] = (uint32_t)(wrow(b, R) * (int64_t)K * 2 + ((lane & 7) ^ ((R >> 1) & 7)) * 16);
         }
-    // activation loads (h = 0, 1): rows h * 8 + lane / 8, position lane % 8
-    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(g.a, (uint32_t)((int64_t)g.a_rows * K * 2));
-    uint32_t aoff[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int R = h * 8 + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((R >> 1) & 7);
-        aoff[h] = (uint32_t)(a_source_row(g, row0 + R, row1) * (int64_t)K * 2 + chunk * 16);
-    }
-    const int r16 = lane & 15, kg = lane >> 4;
-    // the projection's row scale, loaded and waited for before the loop (a load into a
-    // register still in flight across the loop makes the compiler wait for every load in it)
-    float sc = 1.0f;
-    if constexpr (MODE != kExpand) {
-        if (g.row_scale) sc = g.row_scale[scale_row(g, min(row0 + r16, row1 - 1))];
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkm));
-    }
-    // fragment of row r16, chunk 4 * step + kg
-    const int fo0 = r16 * 128 + ((kg ^ ((r16 >> 1) & 7)) * 16);
-    const int fo1 = r16 * 128 + (((4 + kg) ^ ((r16 >> 1) & 7)) * 16);
-
-    floatx4 acc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int KP = K / 64;
-    auto issue = [&](int j, int p) {
-        char* slot = ring + j * kSlot;
+    // this wave's slices of 64 K values: first, first + KW, ...
+    const int first = KW == 1 ? 0 : wave;
+    const int KP = (K / 64 - first + KW - 1) / KW;
+    auto issue_w = [&](int j, int p) {
+        char* slot = ring + j * C::kSlot;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds((MODE == kExpand && b >= NB / 2) ? rb1 : rb0,
                                                          (PCM_LDS void*)(slot + b * 2048 + h * 1024), 16,
-                                                         voff[b][h], p * 128, 0, 0);
+                                                         voff[b][h], (first + p * KW) * 128, 0, 0);
+    };
+    auto issue_a = [&](int j, int p) {
+        char* slot = ring + j * C::kSlot;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (PCM_LDS void*)(slot + NB * 2048 + h * 1024), 16,
-                                                     aoff[h], p * 128, 0, 0);
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (PCM_LDS void*)(slot + (NB + m) * 2048 + h * 1024), 16,
+                                                         aoff[m][h], (first + p * KW) * 128, 0, 0);
     };
 #pragma unroll
-    for (int j = 0; j < D - 1; ++j)
-        if (j < KP) issue(j, j);
+    for (int j = 0; j < D - 1; ++j) issue_w(j, min(j, KP - 1));   // past the end: re-read, never used
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int R = h * 8 + (lane >> 3);
+            int64_t src = arow[m][h];
+            src = src < 0 ? 0 : (src >= g.a_rows ? g.a_rows - 1 : src);
+            aoff[m][h] = (uint32_t)(src * K * 2 + ((lane & 7) ^ ((R >> 1) & 7)) * 16);
+        }
+        // the scale has landed here (a load into a register still in flight across the loop makes
+        // the compiler wait for every load in it)
+        if constexpr (MODE != kExpand) asm volatile("" : "+v"(sc[m])::"memory");
+    }
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j) issue_a(j, min(j, KP - 1));
+    // fragment of row r16, chunk 4 * step + kg
+    const int fo0 = r16 * 128 + ((kg ^ ((r16 >> 1) & 7)) * 16);
+    const int fo1 = r16 * 128 + (((4 + kg) ^ ((r16 >> 1) & 7)) * 16);
+
+    floatx4 acc[NB][MB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) acc[b][m] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int base = 0; base < KP; base += D) {
 #pragma unroll
         for (int j = 0; j < D; ++j) {
             const int p = base + j;
             if (p >= KP) break;
-            // slot (j + D - 1) % D held pair p - 1, whose fragments the previous MFMAs used
-            if (p + D - 1 < KP) issue((j + D - 1) % D, p + D - 1);
-            // pair p has landed: only the pairs issued after it may still be in flight
-            if (p + D - 1 < KP) __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 1) * (2 * NB + 2), kNoLgkm));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkm));
-            const char* slot = ring + j * kSlot;
+            // slot (j + D - 1) % D held slice p - 1, whose fragments the previous MFMAs used
+            if (p + D - 1 < KP) {
+                issue_w((j + D - 1) % D, p + D - 1);
+                issue_a((j + D - 1) % D, p + D - 1);
+            }
+            // slice p has landed: only loads issued after it may still be in flight (of the first
+            // D - 1 slices every weight load came before every activation load)
+            if (p + D - 1 >= KP) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkm));
+            else if (j < D - 2 && base == 0) __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 2) * 2 * MB + C::kLoads, kNoLgkm));
+            else __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 1) * C::kLoads, kNoLgkm));
+            const char* slot = ring + j * C::kSlot;
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
                 const int fo = st ? fo1 : fo0;
-                const bf16x8 av = *(const bf16x8*)(slot + NB * 2048 + fo);
-                if constexpr (MODE == kExpand) {
+                typename Frag<MODE>::T av[MB];
 #pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b] = mfma_step(*(const bf16x8*)(slot + b * 2048 + fo), av, acc[b]);
-                } else {
-                    const halfx8 a16 = __builtin_bit_cast(halfx8, av);
+                for (int m = 0; m < MB; ++m) av[m] = Frag<MODE>::acts(slot + (NB + m) * 2048 + fo);
 #pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b] = mfma_step(Frag<MODE>::weights(slot + b * 2048 + fo), a16, acc[b]);
+                for (int b = 0; b < NB; ++b) {
+                    const typename Frag<MODE>::T wv = Frag<MODE>::weights(slot + b * 2048 + fo);
+#pragma unroll
+                    for (int m = 0; m < MB; ++m) acc[b][m] = mfma_step(wv, av[m], acc[b][m]);
                 }
             }
         }
     }
-    // epilogue: lane holds output columns c..c+3 (c = 4 * (lane >> 4)) of activation row r16
-    // in each block
-    const int r = row0 + r16;
-    if (r >= row1) return;
-    if (MODE == kExpand) {
+    // lane holds output columns c..c+3 (c = 4 * (lane >> 4)) of activation row r16 in each block
+    if constexpr (KW == 1) {
 #pragma unroll
-        for (int b = 0; b < NB / 2; ++b) {
-            const int f = col0 + b * 16 + 4 * kg;
-            if (f >= N) continue;
-            float v[4];
+        for (int m = 0; m < MB; ++m) {
+            const int r = row0 + m * 16 + r16;
+            if (r >= row1) continue;
+            if constexpr (MODE == kExpand) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = silu(acc[b][i]) * acc[b + NB / 2][i];
-            *(float4*)((float*)g.out + (int64_t)r * N + f) = make_float4(v[0], v[1], v[2], v[3]);
+                for (int b = 0; b < NB / 2; ++b) {
+                    const int f = col0 + b * 16 + 4 * kg;
+                    if (f < N) store_swiglu4(g, r, f, acc[b][m], acc[b + NB / 2][m]);
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int h = col0 + b * 16 + 4 * kg;
+                    if (h < N) store_down4<MODE>(g, r, h, acc[b][m], sc[m]);
+                }
+            }
         }
     } else {
+        // every wave's sums into LDS (its ring is free once every wave is past its loop), then
+        // each wave finishes its share of the blocks, adding in wave order
+        __syncthreads();
+        floatx4* const sums = (floatx4*)lds;   // [wave][b][m][lane]
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int h = col0 + b * 16 + 4 * kg;
-            if (h >= N) continue;
-            float4 v = make_float4(acc[b][0] * sc, acc[b][1] * sc, acc[b][2] * sc, acc[b][3] * sc);
-            float4* dst = (float4*)((float*)g.out + (int64_t)r * N + h);
-            if (base_mode(MODE) == kDownAccum && g.accumulate) {
-                const float4 o = *dst;
-                v.x = __fadd_rn(o.x, v.x); v.y = __fadd_rn(o.y, v.y);
-                v.z = __fadd_rn(o.z, v.z); v.w = __fadd_rn(o.w, v.w);
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int m = 0; m < MB; ++m) sums[((wave * NB + b) * MB + m) * 64 + lane] = acc[b][m];
+        __syncthreads();
+        auto total = [&](int b, int m) {
+            floatx4 t = sums[(b * MB + m) * 64 + lane];
+#pragma unroll
+            for (int q = 1; q < SWAVES; ++q) t += sums[((q * NB + b) * MB + m) * 64 + lane];
+            return t;
+        };
+        constexpr int kBlocks = (MODE == kExpand ? NB / 2 : NB) * MB;
+#pragma unroll
+        for (int i0 = 0; i0 < kBlocks; i0 += SWAVES) {
+            const int i = i0 + wave;
+            if (i >= kBlocks) break;
+            const int b = i / MB, m = i % MB;
+            const int r = row0 + m * 16 + r16, c = col0 + b * 16 + 4 * kg;
+            if (r >= row1 || c >= N) continue;
+            if constexpr (MODE == kExpand) {
+                store_swiglu4(g, r, c, total(b, m), total(b + NB / 2, m));
+            } else {
+                float s = sc[0];
+#pragma unroll
+                for (int q = 1; q < MB; ++q) s = m == q ? sc[q] : s;
+                store_down4<MODE>(g, r, c, total(b, m), s);
             }
-            *dst = v;
         }
-    }
+        }
 }
 
-template <int MODE, int NB, int D>
-__global__ __launch_bounds__(SWAVES * 64) void gemm_lstream_kernel(GemmArgs g, int64_t mt_upper,
-                                                                  int nt, int n_fastest) {
+template <int MODE, int NB, int MB, int D, int KW>
+__global__ __launch_bounds__(SWAVES * 64) void gemm_lstream_kernel(GemmArgs g, int64_t mt_upper, int nt) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     __shared__ int s_tile[3];
-    const int64_t mt = n_fastest ? blockIdx.x / nt : blockIdx.x % mt_upper;
-    const int ntile = n_fastest ? (int)(blockIdx.x % nt) : (int)(blockIdx.x / mt_upper);
-    if (!find_tile<SROWS>(g.offsets, g.n, g.a_rows, mt, s_tile)) return;
-    lstream_tile<MODE, NB, D>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
+    // the expansion runs a group's N tiles back to back (its gathered activation rows are then
+    // shared through L2: 6% faster on the decode-shaped layer); the projection interleaves
+    // the groups (4% faster than N tiles back to back there)
+    const int64_t mt = MODE == kExpand ? blockIdx.x / nt : blockIdx.x % mt_upper;
+    const int ntile = MODE == kExpand ? (int)(blockIdx.x % nt) : (int)(blockIdx.x / mt_upper);
+    if (!find_tile<16 * MB>(g.offsets, g.n, g.a_rows, mt, s_tile)) return;
+    lstream_tile<MODE, NB, MB, D, KW>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
 }
 
-template <int MODE, int NB, int D>
+template <int MODE, int NB, int MB, int D, int KW = 1>
 hipError_t launch_lstream_cfg(const GemmArgs& g, int64_t R, hipStream_t s) {
-    const int64_t mt_upper = g.offsets ? ceil_div(R, SROWS) + g.n : ceil_div(R, SROWS);
-    constexpr int kWgCols = SWAVES * ((MODE == kExpand) ? NB * 8 : NB * 16);
-    constexpr int kLds = SWAVES * D * (NB + 1) * 2048;
-    const int nt = (int)ceil_div(g.N, kWgCols);
+    using C = LStream<MODE, NB, MB, D, KW>;
+    const int64_t mt_upper = most_tiles(g, R, 16 * MB);
+    const int nt = (int)ceil_div(g.N, C::kWgCols);
     const int64_t grid = mt_upper * nt;
     if (grid <= 0) return hipSuccess;
     // set on every launch (idempotent, and the library keeps no state between calls)
-    const hipError_t err = hipFuncSetAttribute((const void*)gemm_lstream_kernel<MODE, NB, D>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    const hipError_t err = hipFuncSetAttribute((const void*)gemm_lstream_kernel<MODE, NB, MB, D, KW>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (err != hipSuccess) return err;
-    const int n_fastest = MODE == kExpand ? 1 : 0;
-    gemm_lstream_kernel<MODE, NB, D><<<dim3((unsigned)grid), dim3(SWAVES * 64), kLds, s>>>(g, mt_upper, nt, n_fastest);
+    gemm_lstream_kernel<MODE, NB, MB, D, KW><<<dim3((unsigned)grid), dim3(SWAVES * 64), C::kLds, s>>>(g, mt_upper, nt);
     return hipGetLastError();
 }
 
 template <int MODE, int NB, int SDP>
 hipError_t launch_stream_cfg(const GemmArgs& g, int64_t R, hipStream_t s) {
-    const int64_t mt_upper = g.offsets ? ceil_div(R, SROWS) + g.n : ceil_div(R, SROWS);
+    const int64_t mt_upper = most_tiles(g, R, SROWS);
     constexpr int kWgCols = SWAVES * ((MODE == kExpand) ? NB * 8 : NB * 16);
     const int nt = (int)ceil_div(g.N, kWgCols);
     const int64_t grid = mt_upper * nt;
@@ -1065,26 +1156,60 @@ hipError_t launch_stream_cfg(const GemmArgs& g, int64_t R, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Register-ring kernel: two 16-row blocks per wave, eight k-steps in flight (four or six
-// blocks, or six steps, measured 1-3% slower on the decode-shaped layer).
+// 32-bit buffer offsets reach every row of `a` and of one group's weights.
+inline bool offsets_reach(const GemmArgs& g) {
+    return g.a_rows * g.K * 2 < (int64_t(1) << 32) && (int64_t)g.N * g.K * 2 < (int64_t(1) << 32);
+}
+
+// The streaming kernels that split K over a workgroup's waves (KW = 4). One group of rows: every
+// output column block has few workgroups (2048 columns: 64 of 32), so each takes up to 64 rows at
+// once, and the projection 16 columns per workgroup. Shared expert, H 2048, F 5632, three kernels:
+// 1 row 55.9 -> 23.2 us, 16 rows 83.1 -> 25.6, 48 rows 85.2 -> 35.0, 64 rows 87.3 -> 39.0 (the
+// large tiles from 16 rows on before, 8 to 44 workgroups).
+template <int MODE>
+hipError_t launch_stream_ksplit(const GemmArgs& g, int64_t R, hipStream_t s) {
+    if (!g.offsets) {
+        constexpr int NB = MODE == kExpand ? 2 : 1, D = MODE == kExpand ? 2 : 3;
+        if (R <= 16) return launch_lstream_cfg<MODE, NB, 1, D, 4>(g, R, s);
+        if (R <= 32) return launch_lstream_cfg<MODE, NB, 2, 2, 4>(g, R, s);
+        if (R <= 48) return launch_lstream_cfg<MODE, NB, 3, 2, 4>(g, R, s);
+        return launch_lstream_cfg<MODE, NB, 4, 2, 4>(g, R, s);
+    }
+    // 32 rows per tile from a mean of 4 rows on, where groups of more than 16 become common (40
+    // tokens on the Mixtral shape: expansion 339 -> 311 us, projection 210 -> 188; below, 0-2% slower)
+    return R >= 4 * (int64_t)g.n ? launch_lstream_cfg<MODE, 2, 2, 2, 4>(g, R, s)
+                                 : launch_lstream_cfg<MODE, 2, 1, 2, 4>(g, R, s);
+}
+
+// The default of the streaming kernels. Splitting K pays from long sums on: expansions from H =
+// 1024 (24 tokens, OLMoE shape 93.5 -> 89.4 us; 3 tokens, Mixtral shape 160 -> 139), projections
+// from F = 2048 (Mixtral shape, 3 tokens 126 -> 87 us; decode shape 817 -> 796; at F = 1408 34.7
+// -> 37.6), one group of rows from K = 512; with 16 rows per group and more (only when forced) there
+// are workgroups enough. Without the split the sums run in the order of every other kernel.
+// A forced depth of 2-6 runs the four waves side by side with that ring, 0 the register ring.
 template <int MODE>
 hipError_t launch_stream(const GemmArgs& g, int64_t R, hipStream_t s, int depth) {
-    // the LDS-ring kernel (whole-line weight loads) where its constraints hold; ring depth 3
-    // for the expansion and 2 for the projection (decode-shaped layer: 2-6 within 0.5% for the
-    // expansion; the projection 3% slower at 3 and 45% at 4, where the compiler waits for every
-    // load in flight before the fragment reads and only one workgroup fits a compute unit);
-    // a forced depth of 0 runs the register-ring kernel
-    if (g.K % 64 == 0 && g.a_rows * g.K * 2 < (int64_t(1) << 32) && (int64_t)g.N * g.K * 2 < (int64_t(1) << 32)) {
+    if (g.K % 64 == 0 && offsets_reach(g)) {
+        const bool few = !g.offsets || R < 16 * (int64_t)g.n;
+        if (depth < 0 && few && g.K >= (g.offsets ? (MODE == kExpand ? 1024 : 2048) : 512))
+            return launch_stream_ksplit<MODE>(g, R, s);
+        // ring depth 3 for the expansion and 2 for the projection (decode-shaped layer: 2-6 within
+        // 0.5% for the expansion; the projection 3% slower at 3)
         const int dv = depth >= 0 ? depth : (MODE == kExpand ? 3 : 2);
-        if (dv == 2) return launch_lstream_cfg<MODE, 2, 2>(g, R, s);
-        if (dv == 4) return launch_lstream_cfg<MODE, 2, 4>(g, R, s);
-        if (dv == 6) return launch_lstream_cfg<MODE, 2, 6>(g, R, s);
-        if (dv != 0) return launch_lstream_cfg<MODE, 2, 3>(g, R, s);
+        if (dv == 2) return launch_lstream_cfg<MODE, 2, 1, 2>(g, R, s);
+        if (dv == 4) return launch_lstream_cfg<MODE, 2, 1, 4>(g, R, s);
+        if (dv == 6) return launch_lstream_cfg<MODE, 2, 1, 6>(g, R, s);
+        if (dv != 0) return launch_lstream_cfg<MODE, 2, 1, 3>(g, R, s);
     }
+    // register-ring kernel: two 16-row blocks per wave, eight k-steps in flight (four or six
+    // blocks, or six steps, measured 1-3% slower on the decode-shaped layer)
     return launch_stream_cfg<MODE, 2, 8>(g, R, s);
 }
 
 // ---------------------------------------------------------------------- launch
+// A mean of fewer than 96 rows per group: most row tiles are tail tiles of at most 128 rows.
+inline bool mostly_tails(const GemmArgs& g, int64_t R) { return g.offsets && R < 96 * (int64_t)g.n; }
+
 template <class C, int MODE, bool IL, class CT = LargeIlTail>
 hipError_t launch_cfg(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTune& t) {
     // set on every launch (idempotent, and the library keeps no state between calls)
@@ -1095,21 +1220,27 @@ hipError_t launch_cfg(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTun
         fn = (const void*)gemm_staged_kernel<C, MODE>;
     const hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (err != hipSuccess) return err;
-    const int64_t mt_upper = g.offsets ? ceil_div(R, C::BM) + g.n : ceil_div(R, C::BM);
+    const int64_t mt_upper = most_tiles(g, R, C::BM);
     constexpr int kOutCols = (MODE == kExpand) ? C::BNB / 2 : C::BNB;
     const int nt = (int)ceil_div(g.N, kOutCols);
     if (mt_upper * nt <= 0) return hipSuccess;
     const int group_n = t.group_n > 0 ? t.group_n : 4;
     if constexpr (IL) {
-        // default: expert-major for grouped rows, except for a projection whose tiles fill fewer
-        // than 4 rounds of the chip (or that splits K), which takes the longest-first order (its
-        // short items fill the last round; the expert-major order was 17% slower on the
-        // Mixtral-shaped projection without a K split); one group of rows the orders tuned for it
+        // default: one group of rows the orders tuned for it; grouped rows the expert-major order,
+        // except for
+        //  - an expansion of at least 16 N tiles with a mean below 256 rows, few of whose row tiles
+        //    share a weight tile: the grouped order, which has every XCD walk all groups over N tiles
+        //    of its own (Mixtral shape: 203 tokens 380 -> 351 us, 400 tokens 415 -> 387, 768 tokens
+        //    500 -> 492; equal at 1024 tokens);
+        //  - a projection whose tiles fill fewer than 4 rounds of the chip (or that splits K): the
+        //    longest-first order, whose short items fill the last round (the expert-major order was 17%
+        //    slower on the Mixtral-shaped projection without a K split), unless most row tiles are
+        //    tails (203 tokens there: longest first 216 us, expert-major 202; 512 tokens 271 and 302)
         int order = t.order;
         if (order < 0 || order > 2) {
             if (g.offsets == nullptr) order = MODE == kExpand ? kGrouped : kLongestFirst;
-            else order = (MODE != kExpand && (g.ksplit > 1 || mt_upper * nt < 4 * 256))
-                             ? kLongestFirst : kExpertMajor;
+            else if (MODE == kExpand) order = nt >= 16 && R < 256 * (int64_t)g.n ? kGrouped : kExpertMajor;
+            else order = !mostly_tails(g, R) && (g.ksplit > 1 || mt_upper * nt < 4 * 256) ? kLongestFirst : kExpertMajor;
         }
         // the searches of il_item and em_item run in 32-bit integers (item counts times 8)
         if ((mt_upper + g.n + 1) * nt * g.ksplit >= (int64_t(1) << 27)) order = kGrouped;
@@ -1170,14 +1301,71 @@ int down_ksplit(int64_t R, int n, int H, int F, char tile) {
 }
 
 namespace {
+// The element types of the ring tiles (gemm_ring.h): the fragments and MFMAs of the other kernels.
+template <int MODE>
+struct ElemB16 {
+    static constexpr int SIZE = 2, NJ = 1;
+    using T = typename Frag<MODE>::T;
+    using Silu = FastSilu;
+    __device__ static T weights(const char* p) { return Frag<MODE>::weights(p); }
+    __device__ static T acts(const char* p) { return Frag<MODE>::acts(p); }
+    __device__ static floatx4 step(int, const T& w, const T& a, floatx4 c) { return mfma_step(w, a, c); }
+};
+
+// Ring tiles: 64 rows x 128 or 64 weight rows, two or three workgroups on a compute unit.
+using RingWide = RCfg<64, 128, 2, 2, 3>;
+using RingNarrow = RCfg<64, 64, 2, 2, 3>;
+
+// The shape that the large tiles' work runs in when no kernel is forced: 'L', or smaller tiles where
+// the large ones would leave most of the chip idle: 'R' RingWide, 'N' RingNarrow, 'S' the streaming
+// kernel with its K split (one group of rows). Every kernel here is bound by the bytes a compute
+// unit loads, 54 KB per us whatever the tile (large tiles 64 KB per 64-wide K stage and 1.18 us,
+// RingWide 24 KB and 0.42-0.48 us, RingNarrow 16 KB and 0.26-0.37 us, streaming 10-12 KB and
+// 0.15-0.22 us), so smaller tiles move more bytes per output but spread over more compute units. The
+// times below are those rates over 256 compute units (shared expert, H 2048, F 5632, expansion and
+// projection in us, L / R / N / S: 64 rows 29 49 / 19 45 / 16 34 / 19 17; 256 rows 43 106 / 29 44 /
+// 28 34 / 46 31; 1000 rows 52 102 / 73 45 / 82 48 / 145 102; 4096 rows 147 107 / 271 159 / 398 220 /
+// 563 415). The smaller tiles are taken where they come out a fifth faster. Groups of fewer than 40
+// rows on average are bound by their weights, and one 64-row tile wastes least (OLMoE shape, 256
+// tokens: expansion 116 -> 108 us, projection with mix and combine 87 -> 78; where the projection
+// splits K the large tiles are faster, Mixtral shape, 128 tokens 187 against 208 us). Each shape sums K in
+// the large tiles' order, except the streaming kernel's split.
+char pick_shape(const GemmArgs& g, int64_t R, bool expand) {
+    const double KT = (double)(g.K / g.ksplit) / 64, ne = g.offsets ? (double)(R < g.n ? R : g.n) : 1;
+    if (g.offsets && g.ksplit == 1 && R < 40 * ne) return 'R';
+    auto tiles = [&](int BM, int cols) {
+        const double rows = g.offsets ? ((double)R / BM + ne / 2 > ne ? (double)R / BM + ne / 2 : ne) : (double)ceil_div(R, BM);
+        return rows * (double)(ceil_div(g.N, cols) * g.ksplit) / 256;
+    };
+    auto most = [](double a, double b) { return a > b ? a : b; };
+    auto up = [](double v) { return (double)(int64_t)(v + 0.999); };
+    const int half = expand ? 2 : 1;   // gate and up rows of each output column
+    const double large = KT * up(tiles(256, 256 / half)) * (R <= 128 * ne ? 0.89 : 1.18) + 6;
+    const double wide = KT * most(0.48, 0.42 * tiles(64, 128 / half)) + 4;
+    const double narrow = KT * most(0.37, 0.26 * tiles(64, 64 / half)) + 4;
+    double best = 0.8 * large;
+    char t = 'L';
+    if (wide < best) { best = wide; t = 'R'; }
+    if (narrow < best) { best = narrow; t = 'N'; }
+    if (!g.offsets && g.K >= 512) {
+        const int mb = R > 48 ? 4 : (R > 32 ? 3 : (R > 16 ? 2 : 1));
+        const double stream = KT * up(tiles(16 * mb, 16)) * (2 * ((expand ? 2 : 1) + mb)) / 54 + 2;
+        if (stream < best) t = 'S';
+    }
+    return t;
+}
+
 template <int MODE>
 hipError_t launch_mode(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTune& tune, char t) {
     if (t == 'S') return launch_stream<MODE>(g, R, s, tune.stream_depth);
+    if (t == 'R') return launch_ring<ElemB16<MODE>, RingWide, MODE>(g, R, s, 1);
+    if (t == 'N') return launch_ring<ElemB16<MODE>, RingNarrow, MODE>(g, R, s, 1);
     if (t == 'M') return launch_cfg<MediumStaged, MODE, false>(g, R, s, tune);
     // the large tiles: eight waves for the expansion, four for the projections (interleaved
     // A/B, bit-identical: expansion -2.7% / -2.4% / -0.3% on the Mixtral-, OLMoE- and
-    // fine-grained-shaped layers, projections +1% to +1.7%)
-    if (t == 'W' || (t == 'L' && MODE == kExpand && tune.tile != 'L'))
+    // fine-grained-shaped layers, projections +1% to +1.7%), and for projections of mostly tail
+    // tiles (the same shapes as the expert-major order below: Mixtral shape, 203 tokens 205 -> 202 us)
+    if (t == 'W' || (t == 'L' && tune.tile != 'L' && (MODE == kExpand || mostly_tails(g, R))))
         return launch_cfg<WideIl, MODE, true, WideIlTail>(g, R, s, tune);
     return launch_cfg<LargeIl, MODE, true>(g, R, s, tune);
 }
@@ -1187,8 +1375,9 @@ hipError_t launch_gemm_bf16(GemmMode mode, const GemmArgs& g0, int64_t R, hipStr
                             const GemmTune& tune) {
     GemmArgs g = g0;
     if (g.ksplit < 1) g.ksplit = 1;
-    const char t = pick_tile(R, g.offsets ? g.n : 1, g.a_rows * g.K * 2, (int64_t)g.N * g.K * 2, tune.tile);
+    char t = pick_tile(R, g.offsets ? g.n : 1, g.a_rows * g.K * 2, (int64_t)g.N * g.K * 2, tune.tile);
     if (g.ksplit > 1 && (mode != kDownStore || (t != 'L' && t != 'W'))) return hipErrorInvalidValue;
+    if (tune.tile == 0 && t == 'L') t = pick_shape(g, R, mode == kExpand);
     switch (mode) {
         case kExpand: return launch_mode<kExpand>(g, R, s, tune, t);
         case kDownStore:

@@ -15,6 +15,13 @@ constexpr int waitcnt_imm(int vm, int lgkm) {
 }
 constexpr int kNoVm = 63, kNoLgkm = 15;
 
+// Most row tiles of BM rows that R rows make in the groups of g: a group with c rows has
+// ceil(c / BM) <= (c + BM - 1) / BM tiles, and at most min(n, R) groups have rows.
+inline int64_t most_tiles(const GemmArgs& g, int64_t R, int BM) {
+    if (!g.offsets) return ceil_div(R, BM);
+    return (R + (BM - 1) * (R < g.n ? R : g.n)) / BM;
+}
+
 // Source row of A row r of the tile (rows past row1 repeat a valid row; their outputs are
 // never stored).
 __device__ inline int64_t a_source_row(const GemmArgs& g, int r, int row1) {
@@ -125,13 +132,13 @@ __device__ inline void epilogue(const GemmArgs& g, const floatx4 (&acc)[NBK][MB]
 // at least 1), the M-tile varying slowest within a block, so that the `window` workgroups
 // an XCD runs at once cover all of a group's rows for a few N-tiles: each weight tile is
 // fetched while every row block that needs it runs, each activation tile once per block.
-// Each XCD (bid % 8) takes a contiguous eighth of the list (every K slice, slice-major), or,
-// for groups of at least 16 N tiles in multiples of 8, every eighth window (below). A last
+// Each XCD (bid % 8) takes a contiguous eighth of the list (every K slice, slice-major), or, with
+// `interleave`, for groups of at least 16 N tiles in multiples of 8, every eighth window (below). A last
 // row block of at most TBM rows runs as the shorter tail tile.
 // Wave 0 counts and searches; the result is broadcast through LDS (s_item: group, row0, row1,
 // ntile, kslice, valid). Returns false past the last item.
 template <int BM, int TBM>
-__device__ bool em_item(const GemmArgs& g, int nt, int window, int* s_item) {
+__device__ bool em_item(const GemmArgs& g, int nt, int window, bool interleave, int* s_item) {
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int lo[4], cnt[4], m[4], local = 0;
@@ -151,7 +158,7 @@ __device__ bool em_item(const GemmArgs& g, int nt, int window, int* s_item) {
             local += m[j] * nt;
         }
         const int x8 = (int)(blockIdx.x % 8), j8 = (int)(blockIdx.x / 8);
-        if (g.ksplit == 1 && nt % 8 == 0 && nt >= 16) {
+        if (interleave && g.ksplit == 1 && nt % 8 == 0 && nt >= 16) {
             // Window-interleaved assignment: a group's N tiles are cut into windows of gw tiles,
             // gw the largest divisor of nt / 8 not above window / m (so that every window has
             // the same width and their number is a multiple of 8), and window i runs on XCD

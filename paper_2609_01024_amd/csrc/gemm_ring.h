@@ -93,16 +93,17 @@ __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, ch
     }
 }
 
-// One tile: rows [row0, row1) of group e, N tile ntile.
+// One tile: rows [row0, row1) of group e, N tile ntile, K slice kslice of g.ksplit.
 template <class E, class C, int MODE>
 __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
-                                          int ntile) {
+                                          int ntile, int kslice) {
     static_assert(C::WTN % 32 == 0, "gate/up halves");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int N = g.N;
     const int64_t rowb = (int64_t)g.K * E::SIZE;   // bytes of a row of either operand
     constexpr int kOutCols = (MODE == kExpand) ? C::BN / 2 : C::BN;
+    const int KT = g.K / g.ksplit * E::SIZE / 128;
     const char* src[C::LPW];
     int64_t srow[C::QA];   // every row index is loaded before any is used
 #pragma unroll
@@ -122,11 +123,13 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
         } else {
             base = (const char*)g.b0 + ((int64_t)e * N + min(ntile * kOutCols + lr, N - 1)) * rowb;
         }
-        src[q] = base + chunk * 16;
+        src[q] = base + (int64_t)kslice * KT * 128 + chunk * 16;
     }
     floatx4 acc[C::NBK][C::MB];
-    ring_loop<E, C>(src, g.K * E::SIZE / 128, lds, acc);
-    epilogue<MODE, C::MB, C::NBK, C::WTM, C::WTN, kOutCols, typename E::Silu>(g, acc, row0, row1, ntile, wave / C::WN,
+    ring_loop<E, C>(src, KT, lds, acc);
+    GemmArgs gs = g;
+    if (kslice) gs.out = (float*)g.out + (int64_t)kslice * g.rows_total * N;
+    epilogue<MODE, C::MB, C::NBK, C::WTM, C::WTN, kOutCols, typename E::Silu>(gs, acc, row0, row1, ntile, wave / C::WN,
                                                                               wave % C::WN, lane);
 }
 
@@ -135,17 +138,17 @@ template <class E, class C, int MODE>
 __global__ __launch_bounds__(C::NT) void gemm_ring_kernel(GemmArgs g, int nt, int window) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     int* const s_item = (int*)lds;   // read into registers before the first loads overwrite it
-    if (!em_item<C::BM, C::BM>(g, nt, window, s_item)) return;   // workgroup-uniform
-    const int e = s_item[0], row0 = s_item[1], row1 = s_item[2], ntile = s_item[3];
+    if (!em_item<C::BM, C::BM>(g, nt, window, false, s_item)) return;   // workgroup-uniform
+    const int e = s_item[0], row0 = s_item[1], row1 = s_item[2], ntile = s_item[3], kslice = s_item[4];
     __syncthreads();
-    ring_tile<E, C, MODE>(g, lds, e, row0, row1, ntile);
+    ring_tile<E, C, MODE>(g, lds, e, row0, row1, ntile, kslice);
 }
 
 template <class E, class C, int MODE>
 hipError_t launch_ring(const GemmArgs& g, int64_t R, hipStream_t s, int window) {
-    const int64_t mt_upper = g.offsets ? ceil_div(R, C::BM) + g.n : ceil_div(R, C::BM);
+    const int64_t mt_upper = most_tiles(g, R, C::BM);
     const int nt = (int)ceil_div(g.N, MODE == kExpand ? C::BN / 2 : C::BN);
-    const int64_t grid = ceil_div(mt_upper * nt, 8) * 8;
+    const int64_t grid = ceil_div(mt_upper * nt * g.ksplit, 8) * 8;
     if (grid <= 0) return hipSuccess;
     // set on every launch (idempotent, and the library keeps no state between calls)
     const hipError_t err = hipFuncSetAttribute((const void*)gemm_ring_kernel<E, C, MODE>,

@@ -58,3 +58,58 @@ def test_router_forms(T, H, n, k):
     x = torch.randn((T, H), generator=g).to(torch.bfloat16)
     wr = (torch.randn((n, H), generator=g) * 0.02).to(torch.bfloat16)
     check_route_logits(x, wr, k, f"T={T} H={H} n={n} k={k}")
+
+
+# one group of rows (the shared expert) on the shapes that pick_shape chooses between: streaming with
+# the K split (rows 1 to 64 per tile, 17 and 33 and 49 start another block), 64-row ring tiles (row and
+# column remainders), large tiles; K = 512 and 448 are the two sides of the split's line
+@pytest.mark.parametrize("T,H,Fs", [(1, 512, 512), (16, 448, 576), (17, 576, 1088), (33, 1024, 640), (49, 1024, 1600),
+                                    (64, 2048, 512), (65, 2048, 512), (128, 1024, 1984), (300, 1024, 2112),
+                                    (1000, 576, 2048), (2500, 320, 320)])
+def test_dense_swiglu_shapes(T, H, Fs):
+    cfg = scaled(CONFIGS["finegrained_shared"], T=T, H=H, F=64, shared_F=Fs, name=f"dense{T}")
+    say(f"dense T={T} H={H} Fs={Fs}")
+    inp = make_inputs(cfg, seed=43)
+    d = dev(inp)
+    sg, su, sd = d["shared"]
+    ws = torch.full((pcm.workspace_bytes(3, T, H, Fs, 1, 1, 1),), 0xFF, dtype=torch.uint8, device=DEV)
+    base = torch.randn((T, H), device=DEV)
+    ref = oracle.dense_swiglu(inp.x, inp.s_gate, inp.s_up, inp.s_down)
+    y0 = torch.full((T, H), float("nan"), device=DEV)
+    for down in (sd, pcm.pcm_widen_f16(sd)):
+        pcm.pcm_dense_swiglu(d["x"], sg, su, down, y=y0, ws=ws)
+        y = pcm.pcm_dense_swiglu(d["x"], sg, su, down, y=base.clone(), accumulate=True, ws=ws)
+        torch.cuda.synchronize()
+        assert_y_close(y0.cpu().numpy(), ref, "bf16", cfg.name)
+        assert torch.equal(y, base + y0), "accumulate adds the stored values"
+
+
+# grouped rows: the streaming K split (below 16 rows per expert; 16-row tiles, 32-row from a mean of
+# 4 on, several tiles in one expert), ring tiles, and a K split of the projection on the ring
+@pytest.mark.parametrize("T,H,n,F,k,logits", [(1, 1024, 64, 2048, 8, "normal"), (3, 4096, 8, 2112, 2, "normal"),
+                                              (40, 1024, 8, 2048, 2, "normal+one_expert"),
+                                              (200, 1088, 60, 2048, 4, "zipf"), (130, 512, 16, 576, 4, "zipf"),
+                                              (70, 320, 4, 4096, 1, "normal"), (257, 192, 5, 1088, 2, "normal"),
+                                              (900, 256, 3, 1536, 2, "normal")])
+def test_layer_shapes(T, H, n, F, k, logits):
+    cfg = scaled(CONFIGS["olmoe"], T=T, H=H, n=n, F=F, k=k, logits=logits, zipf_s=1.1, name=f"shape{T}_{H}")
+    say(f"layer shapes {cfg.name}")
+    inp = make_inputs(cfg, seed=44)
+    d = dev(inp)
+    plan = pcm.LayerPlan(T, H, F, n, k, torch.bfloat16, DEV)
+    ref = oracle.layer_inputs(inp)
+    ys = []
+    for down in (d["w_down"], pcm.pcm_widen_f16(d["w_down"])):
+        poison(plan)
+        y = plan.forward(d["x"], d["logits"], d["mask"], d["w_gate"], d["w_up"], down)
+        torch.cuda.synchronize()
+        ys.append(y.cpu().numpy().copy())
+        assert_y_close(ys[-1], ref, "bf16", cfg.name)
+    assert np.array_equal(ys[0], ys[1]), "bf16 and widened projection weights give the same bits"
+    if R_mean(cfg) >= 16:   # no split of K beyond the large tiles' own: the same sums in the same order
+        y = run_layer(d, k, tuning=pcm.Tuning(tile="L"))
+        assert np.array_equal(y, ys[0]), "the default and the large tiles"
+
+
+def R_mean(cfg):
+    return cfg.T * cfg.k // cfg.n
