@@ -88,6 +88,25 @@ __device__ inline uint64_t wave_max_u64(uint64_t v) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Exclusive scan of v over threads 0..kMaxN-1 of the workgroup (its first four waves; every
+// thread of the workgroup must call it): wave scans by DPP, then the wave totals.
+// Returns the exclusive prefix to threads < kMaxN and the total in *total for all threads.
+__device__ inline int scan_columns(int v, int* wave_tot, int* total) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int incl = wave_incl_scan_i32(v);
+    if (tid < kMaxN && lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    int base = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < kMaxN / 64; ++q) {
+        const int c = wave_tot[q];
+        base += q < wave ? c : 0;
+        all += c;
+    }
+    *total = all;
+    return base + incl - v;
+}
+
 // Launchers (each returns hipGetLastError() of its launches).
 hipError_t launch_route(const float* logits, int64_t T, int n, int k, int32_t* ids, float* w,
                         hipStream_t s);
@@ -198,10 +217,21 @@ hipError_t launch_residual(void* h, const float* y, int64_t N, bool bf16, hipStr
 // weight fragment), count values.
 hipError_t launch_widen_f16(const uint16_t* src, int64_t count, uint16_t* dst, hipStream_t s);
 
-// Grouped dispatch of counts[t] <= K distinct experts per token (ids [T,K]).
-hipError_t launch_dispatch(const int32_t* ids, const int32_t* counts, int64_t T, int n, int K,
-                           int32_t* offsets, int32_t* row_token, int32_t* row_slot,
-                           int32_t* row_of, int32_t* block_counts, hipStream_t s);
+// Grouped dispatch of counts[t] <= K distinct experts per token (ids [T,K]): both sides of the
+// scored router, the sources (side 0) and the targets, in the same launches.
+struct DispatchSide {
+    const int32_t* ids;
+    const int32_t* counts;
+    int32_t* offsets;
+    int32_t* row_token;
+    int32_t* row_slot;
+    int32_t* row_of;
+    int32_t* block_counts;   // build_paths_ws_bytes(T, n)
+};
+struct DispatchSides {
+    DispatchSide s[2];
+};
+hipError_t launch_dispatch(const DispatchSides& d, int64_t T, int n, int K, hipStream_t s);
 
 // Per-path execution (baselines): path rows keyed by the target (key_is_target = 1) or the
 // source slot of each path, expanded in place from the top-k dispatch rows.

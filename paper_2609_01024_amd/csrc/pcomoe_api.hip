@@ -615,13 +615,12 @@ pcm_status pcm_route_scored(const float* g_base, const float* g_tgt, float lambd
                                        out->n_src, out->src_expert, out->n_tgt, out->tgt_expert,
                                        out->path_bits, out->beta, s);
     if (e != hipSuccess) return PCM_ERR_HIP;
-    int32_t* bc = (int32_t*)ws;
-    e = launch_dispatch(out->src_expert, out->n_src, T, n, K, out->src_offsets, out->src_row_token,
-                        out->src_row_slot, out->src_row_of, bc, s);
-    if (e != hipSuccess) return PCM_ERR_HIP;
-    return from_hip(launch_dispatch(out->tgt_expert, out->n_tgt, T, n, K, out->tgt_offsets,
-                                    out->tgt_row_token, out->tgt_row_slot, out->tgt_row_of,
-                                    one ? (int32_t*)((char*)ws + one) : nullptr, s));
+    const DispatchSides d = {{{out->src_expert, out->n_src, out->src_offsets, out->src_row_token,
+                               out->src_row_slot, out->src_row_of, (int32_t*)ws},
+                              {out->tgt_expert, out->n_tgt, out->tgt_offsets, out->tgt_row_token,
+                               out->tgt_row_slot, out->tgt_row_of,
+                               one ? (int32_t*)((char*)ws + one) : nullptr}}};
+    return from_hip(launch_dispatch(d, T, n, K, s));
 }
 
 pcm_status pcm_expand_scored_tuned(pcm_dtype dtype, const void* x, const void* w_gate,

@@ -92,25 +92,6 @@ __device__ inline float readlane_f32(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Exclusive scan of v over threads 0..kMaxN-1 of the workgroup (its first four waves; every
-// thread of the workgroup must call it): wave scans by DPP, then the wave totals.
-// Returns the exclusive prefix to threads < kMaxN and the total in *total for all threads.
-__device__ inline int scan_columns(int v, int* wave_tot, int* total) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int incl = wave_incl_scan_i32(v);
-    if (tid < kMaxN && lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    int base = 0, all = 0;
-#pragma unroll
-    for (int q = 0; q < kMaxN / 64; ++q) {
-        const int c = wave_tot[q];
-        base += q < wave ? c : 0;
-        all += c;
-    }
-    *total = all;
-    return base + incl - v;
-}
-
 // Logits of token t (zeros past T) as this lane's EPL values.
 template <int EPL>
 __device__ inline void load_logits(const float* logits, int64_t t, int64_t T, int n, int lane,
