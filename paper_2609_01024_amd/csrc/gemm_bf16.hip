@@ -76,18 +76,12 @@ __device__ bool find_tile(const int32_t* __restrict__ offsets, int n, int64_t a_
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         if (lane == 0) s_tile[0] = -1;
-        int cnt[4], local = 0, lo[4];
+        int lo[4], rows[4], cnt[4], local = 0;
+        group_bounds(offsets, n, a_rows, lane, lo, rows);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int x = lane * 4 + j;
-            int c = 0, b = 0;
-            if (x < n) {
-                b = offsets[x];
-                c = (int)ceil_div(offsets[x + 1] - b, BM);
-            }
-            cnt[j] = c;
-            lo[j] = b;
-            local += c;
+            cnt[j] = (rows[j] + BM - 1) / BM;
+            local += cnt[j];
         }
         const int incl = wave_incl_scan_i32(local);
         int start = incl - local;
@@ -98,7 +92,7 @@ __device__ bool find_tile(const int32_t* __restrict__ offsets, int n, int64_t a_
                 const int r0 = lo[j] + (int)(mt - start) * BM;
                 s_tile[0] = x;
                 s_tile[1] = r0;
-                s_tile[2] = min(offsets[x + 1], r0 + BM);
+                s_tile[2] = min(lo[j] + rows[j], r0 + BM);
             }
             start += cnt[j];
         }
@@ -545,21 +539,13 @@ template <int BM, int TBM>
 __device__ bool il_item(const GemmArgs& g, int nt, int GN, int* s_item) {
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
-        int lo[4], hi[4], full[4], nl[4], ns[4], suml = 0, sums = 0;
+        int lo[4], cnt[4], hi[4], full[4], nl[4], ns[4], suml = 0, sums = 0;
+        group_bounds(g.offsets, g.n, g.a_rows, lane, lo, cnt);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int x = lane * 4 + j;
-            int c = 0, b = 0;
-            if (g.offsets == nullptr) {
-                if (x == 0) c = (int)g.a_rows;
-            } else if (x < g.n) {
-                b = g.offsets[x];
-                c = g.offsets[x + 1] - b;
-            }
-            const int rem = c % BM;
-            lo[j] = b;
-            hi[j] = b + c;
-            full[j] = c / BM;
+            const int rem = cnt[j] % BM;
+            hi[j] = lo[j] + cnt[j];
+            full[j] = cnt[j] / BM;
             nl[j] = full[j] + (rem > TBM ? 1 : 0);
             ns[j] = (rem > 0 && rem <= TBM) ? 1 : 0;
             suml += nl[j];

@@ -22,6 +22,29 @@ inline int64_t most_tiles(const GemmArgs& g, int64_t R, int BM) {
     return (R + (BM - 1) * (R < g.n ? R : g.n)) / BM;
 }
 
+// First row and row count of groups 4 * lane .. 4 * lane + 3 (0 rows past n; without offsets one group
+// of a_rows rows). The five offsets are loaded without branches and waited for once: behind the bounds
+// check of each group they were four loads one after another, 1.5 us of every workgroup's start.
+__device__ __forceinline__ void group_bounds(const int32_t* __restrict__ offsets, int n, int64_t a_rows, int lane,
+                                             int (&lo)[4], int (&cnt)[4]) {
+    if (offsets == nullptr) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            lo[j] = 0;
+            cnt[j] = lane == 0 && j == 0 ? (int)a_rows : 0;
+        }
+        return;
+    }
+    int o[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) o[j] = offsets[min(lane * 4 + j, n)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        lo[j] = o[j];
+        cnt[j] = o[j + 1] - o[j];   // past n both are offsets[n]
+    }
+}
+
 // Source row of A row r of the tile (rows past row1 repeat a valid row; their outputs are
 // never stored).
 __device__ inline int64_t a_source_row(const GemmArgs& g, int r, int row1) {
@@ -142,19 +165,10 @@ __device__ bool em_item(const GemmArgs& g, int nt, int window, bool interleave, 
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         int lo[4], cnt[4], m[4], local = 0;
+        group_bounds(g.offsets, g.n, g.a_rows, lane, lo, cnt);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int x = lane * 4 + j;
-            int c = 0, b = 0;
-            if (g.offsets == nullptr) {
-                if (x == 0) c = (int)g.a_rows;
-            } else if (x < g.n) {
-                b = g.offsets[x];
-                c = g.offsets[x + 1] - b;
-            }
-            lo[j] = b;
-            cnt[j] = c;
-            m[j] = (c + BM - 1) / BM;
+            m[j] = (cnt[j] + BM - 1) / BM;
             local += m[j] * nt;
         }
         const int x8 = (int)(blockIdx.x % 8), j8 = (int)(blockIdx.x / 8);
@@ -181,46 +195,49 @@ __device__ bool em_item(const GemmArgs& g, int nt, int window, bool interleave, 
             // on a compute unit fell from 4.8 to 1.1 us, the expansion 0.7% faster (its tiles
             // run slower with the compute units fuller, the clock falling under the load).
             const int n8 = nt / 8;
-            int gw[4], mf[4], xl = 0;
+            int xl = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int last = cnt[j] - (m[j] - 1) * BM;   // rows of the last row block
-                mf[j] = (m[j] > 0 && last <= TBM) ? m[j] - 1 : m[j];
-                const int lim = window / (mf[j] > 0 ? mf[j] : 1);
-                int d = lim < 1 ? 1 : (lim > n8 ? n8 : lim);
-                while (n8 % d != 0) --d;
-                gw[j] = d;
-                xl += m[j] * n8;
-            }
+            for (int j = 0; j < 4; ++j) xl += m[j] * n8;
             const int xincl = wave_incl_scan_i32(xl);
             const bool valid = j8 < __builtin_amdgcn_readlane(xincl, 63);
             if (lane == 0) s_item[5] = valid ? 1 : 0;
             if (valid) {
-                int start = xincl - xl;
+                // this lane's group that holds item j8 (at most one lane has one); the divisions are
+                // then done once, by that lane
+                int start = xincl - xl, hit = -1, q = 0, mm_ = 0, lo_ = 0, cnt_ = 0;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int items = m[j] * n8;
-                    if (j8 >= start && j8 < start + items) {
-                        const int q = j8 - start;
-                        int mm, col;
-                        if (q < mf[j] * n8) {              // the full row blocks, window by window
-                            const int gsize = gw[j] * mf[j];
-                            const int kw = q / gsize, in = q - kw * gsize;
-                            mm = in / gw[j];
-                            col = (kw * 8 + x8) * gw[j] + (in - mm * gw[j]);   // window kw * 8 + x8
-                        } else {                           // the tail row block, same N tiles
-                            const int t = q - mf[j] * n8;
-                            mm = m[j] - 1;
-                            col = ((t / gw[j]) * 8 + x8) * gw[j] + t % gw[j];
-                        }
-                        const int r0 = lo[j] + mm * BM;
-                        s_item[0] = lane * 4 + j;
-                        s_item[1] = r0;
-                        s_item[2] = min(lo[j] + cnt[j], r0 + BM);
-                        s_item[3] = col;
-                        s_item[4] = 0;
+                    const bool in = j8 >= start && j8 < start + m[j] * n8;
+                    hit = in ? j : hit;
+                    q = in ? j8 - start : q;
+                    mm_ = in ? m[j] : mm_;
+                    lo_ = in ? lo[j] : lo_;
+                    cnt_ = in ? cnt[j] : cnt_;
+                    start += m[j] * n8;
+                }
+                if (hit >= 0) {
+                    const int last = cnt_ - (mm_ - 1) * BM;   // rows of the last row block
+                    const int mf = last <= TBM ? mm_ - 1 : mm_;
+                    const int lim = window / (mf > 0 ? mf : 1);
+                    int gw = lim < 1 ? 1 : (lim > n8 ? n8 : lim);
+                    while (n8 % gw != 0) --gw;
+                    int mm, col;
+                    if (q < mf * n8) {              // the full row blocks, window by window
+                        const int gsize = gw * mf;
+                        const int kw = q / gsize, in = q - kw * gsize;
+                        mm = in / gw;
+                        col = (kw * 8 + x8) * gw + (in - mm * gw);   // window kw * 8 + x8
+                    } else {                        // the tail row block, same N tiles
+                        const int t = q - mf * n8;
+                        mm = mm_ - 1;
+                        col = ((t / gw) * 8 + x8) * gw + t % gw;
                     }
-                    start += items;
+                    const int r0 = lo_ + mm * BM;
+                    s_item[0] = lane * 4 + hit;
+                    s_item[1] = r0;
+                    s_item[2] = min(lo_ + cnt_, r0 + BM);
+                    s_item[3] = col;
+                    s_item[4] = 0;
                 }
             }
         } else {
@@ -234,26 +251,30 @@ __device__ bool em_item(const GemmArgs& g, int nt, int window, bool interleave, 
                 const int item = l0 + j8;
                 const int kslice = item / Tt;
                 const int id = item - kslice * Tt;
-                int start = incl - local;
+                int start = incl - local, hit = -1, l = 0, mm_ = 1, lo_ = 0, cnt_ = 0;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int items = m[j] * nt;
-                    if (id >= start && id < start + items) {
-                        const int l = id - start;
-                        int gn = window / m[j];
-                        gn = gn < 1 ? 1 : (gn > nt ? nt : gn);
-                        const int gsize = gn * m[j];
-                        const int grp = l / gsize, in = l - grp * gsize;
-                        const int gcols = min(gn, nt - grp * gn);
-                        const int mm = in / gcols;
-                        const int r0 = lo[j] + mm * BM;
-                        s_item[0] = lane * 4 + j;
-                        s_item[1] = r0;
-                        s_item[2] = min(lo[j] + cnt[j], r0 + BM);
-                        s_item[3] = grp * gn + (in - mm * gcols);
-                        s_item[4] = kslice;
-                    }
-                    start += items;
+                    const bool in = id >= start && id < start + m[j] * nt;
+                    hit = in ? j : hit;
+                    l = in ? id - start : l;
+                    mm_ = in ? m[j] : mm_;
+                    lo_ = in ? lo[j] : lo_;
+                    cnt_ = in ? cnt[j] : cnt_;
+                    start += m[j] * nt;
+                }
+                if (hit >= 0) {
+                    int gn = window / mm_;
+                    gn = gn < 1 ? 1 : (gn > nt ? nt : gn);
+                    const int gsize = gn * mm_;
+                    const int grp = l / gsize, in = l - grp * gsize;
+                    const int gcols = min(gn, nt - grp * gn);
+                    const int mm = in / gcols;
+                    const int r0 = lo_ + mm * BM;
+                    s_item[0] = lane * 4 + hit;
+                    s_item[1] = r0;
+                    s_item[2] = min(lo_ + cnt_, r0 + BM);
+                    s_item[3] = grp * gn + (in - mm * gcols);
+                    s_item[4] = kslice;
                 }
             }
         }
