@@ -1152,14 +1152,25 @@ inline bool offsets_reach(const GemmArgs& g) {
 // once, and the projection 16 columns per workgroup. Shared expert, H 2048, F 5632, three kernels:
 // 1 row 55.9 -> 23.2 us, 16 rows 83.1 -> 25.6, 48 rows 85.2 -> 35.0, 64 rows 87.3 -> 39.0 (the
 // large tiles from 16 rows on before, 8 to 44 workgroups).
+//
+// 16-column blocks per workgroup: one, or two where one makes more workgroups than there are compute
+// units (the activations are then fetched half as often: 48 rows, H 2048, F 5632, the three kernels
+// 33.8 -> 30.6 us).
+inline int one_group_blocks(const GemmArgs& g, int64_t R) {
+    return ceil_div(R, 64) * ceil_div(g.N, 16) > 256 ? 2 : 1;
+}
 template <int MODE>
 hipError_t launch_stream_ksplit(const GemmArgs& g, int64_t R, hipStream_t s) {
     if (!g.offsets) {
-        constexpr int NB = MODE == kExpand ? 2 : 1, D = MODE == kExpand ? 2 : 3;
-        if (R <= 16) return launch_lstream_cfg<MODE, NB, 1, D, 4>(g, R, s);
-        if (R <= 32) return launch_lstream_cfg<MODE, NB, 2, 2, 4>(g, R, s);
-        if (R <= 48) return launch_lstream_cfg<MODE, NB, 3, 2, 4>(g, R, s);
-        return launch_lstream_cfg<MODE, NB, 4, 2, 4>(g, R, s);
+        constexpr int E = MODE == kExpand ? 2 : 1;   // weight blocks of 16 output columns
+        auto go = [&](auto nb) {
+            constexpr int NB = decltype(nb)::value;
+            if (R <= 16) return launch_lstream_cfg<MODE, NB, 1, 3, 4>(g, R, s);
+            if (R <= 32) return launch_lstream_cfg<MODE, NB, 2, 2, 4>(g, R, s);
+            if (R <= 48) return launch_lstream_cfg<MODE, NB, 3, 2, 4>(g, R, s);
+            return launch_lstream_cfg<MODE, NB, 4, 2, 4>(g, R, s);
+        };
+        return one_group_blocks(g, R) == 2 ? go(std::integral_constant<int, 2 * E>()) : go(std::integral_constant<int, E>());
     }
     // 32 rows per tile from a mean of 4 rows on, where groups of more than 16 become common (40
     // tokens on the Mixtral shape: expansion 339 -> 311 us, projection 210 -> 188; below, 0-2% slower)
@@ -1301,6 +1312,8 @@ struct ElemB16 {
 // Ring tiles: 64 rows x 128 or 64 weight rows, two or three workgroups on a compute unit.
 using RingWide = RCfg<64, 128, 2, 2, 3>;
 using RingNarrow = RCfg<64, 64, 2, 2, 3>;
+using RingWideTail = RCfg<32, 128, 2, 2, 3>;
+using RingNarrowTail = RCfg<32, 64, 2, 2, 4>;
 
 // The shape that the large tiles' work runs in when no kernel is forced: 'L', or smaller tiles where
 // the large ones would leave most of the chip idle: 'R' RingWide, 'N' RingNarrow, 'S' the streaming
@@ -1335,7 +1348,8 @@ char pick_shape(const GemmArgs& g, int64_t R, bool expand) {
     if (narrow < best) { best = narrow; t = 'N'; }
     if (!g.offsets && g.K >= 512) {
         const int mb = R > 48 ? 4 : (R > 32 ? 3 : (R > 16 ? 2 : 1));
-        const double stream = KT * up(tiles(16 * mb, 16)) * (2 * ((expand ? 2 : 1) + mb)) / 54 + 2;
+        const int nb = one_group_blocks(g, R);
+        const double stream = KT * up(tiles(16 * mb, 16 * nb)) * (2 * ((expand ? 2 : 1) * nb + mb)) / 54 + 3.5;
         if (stream < best) t = 'S';
     }
     return t;
@@ -1344,8 +1358,8 @@ char pick_shape(const GemmArgs& g, int64_t R, bool expand) {
 template <int MODE>
 hipError_t launch_mode(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTune& tune, char t) {
     if (t == 'S') return launch_stream<MODE>(g, R, s, tune.stream_depth);
-    if (t == 'R') return launch_ring<ElemB16<MODE>, RingWide, MODE>(g, R, s, 1);
-    if (t == 'N') return launch_ring<ElemB16<MODE>, RingNarrow, MODE>(g, R, s, 1);
+    if (t == 'R') return launch_ring<ElemB16<MODE>, RingWide, RingWideTail, MODE>(g, R, s, 1);
+    if (t == 'N') return launch_ring<ElemB16<MODE>, RingNarrow, RingNarrowTail, MODE>(g, R, s, 1);
     if (t == 'M') return launch_cfg<MediumStaged, MODE, false>(g, R, s, tune);
     // the large tiles: eight waves for the expansion, four for the projections (interleaved
     // A/B, bit-identical: expansion -2.7% / -2.4% / -0.3% on the Mixtral-, OLMoE- and

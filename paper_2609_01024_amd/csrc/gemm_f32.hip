@@ -24,7 +24,8 @@ struct ElemF32 {
 // (154 TFLOP/s in a large dense product here) where tiles are many: 4000 tokens, 8 experts, top-2,
 // H 1024, F 2048: expansion 1051 -> 576 us (117 TFLOP/s), projection with mix and combine 552 ->
 // 353 us, against the vector-ALU tiles before. 64 x 128 and 128 x 128 tiles measured 0-5% and 3-40%
-// slower (fewer workgroups to overlap, a longer last round), a ring of two slices 2-8%.
+// slower (fewer workgroups to overlap, a longer last round), a ring of two slices 2-8%, 32-row tiles for
+// the last rows of a group -1% to +8%, a deeper ring for the 32 x 64 tiles 0-30%.
 using WideF32 = RCfg<64, 64, 2, 2, 3>;
 using NarrowF32 = RCfg<32, 64, 2, 2, 4>;
 
@@ -36,8 +37,8 @@ hipError_t launch_mode_f32(const GemmArgs& g, int64_t R, hipStream_t s) {
     // above, the larger ones: 777 tokens, 16 experts, top-4: 100 against 157 us (expansion, F 960).
     const int64_t groups = g.offsets ? (R < g.n ? R : g.n) : 0;
     const int64_t tiles = (R / 32 + groups + (g.offsets ? 0 : 1)) * ceil_div(g.N, MODE == kExpand ? 32 : 64) / 2;
-    return tiles >= 768 ? launch_ring<ElemF32, WideF32, MODE>(g, R, s, 1)
-                        : launch_ring<ElemF32, NarrowF32, MODE>(g, R, s, 1);
+    return tiles >= 768 ? launch_ring<ElemF32, WideF32, WideF32, MODE>(g, R, s, 1)
+                        : launch_ring<ElemF32, NarrowF32, NarrowF32, MODE>(g, R, s, 1);
 }
 
 }  // namespace

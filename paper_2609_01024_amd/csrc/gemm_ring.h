@@ -133,28 +133,32 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
                                                                               wave % C::WN, lane);
 }
 
-// Workgroups walk the expert-major order of em_item with the window `window`.
-template <class E, class C, int MODE>
+// Workgroups walk the expert-major order of em_item with the window `window`. A group's last tile with
+// at most CT::BM rows runs as the smaller tile CT (the same columns), sparing the loads of padding
+// rows (bf16, one group of 150 rows, H 2048, F 5632: three kernels 47.2 -> 38.5 us; CT = C: none).
+template <class E, class C, class CT, int MODE>
 __global__ __launch_bounds__(C::NT) void gemm_ring_kernel(GemmArgs g, int nt, int window) {
+    static_assert(CT::NT == C::NT && CT::BN == C::BN && CT::BM <= C::BM && CT::LDS_BYTES <= C::LDS_BYTES, "tail tile");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     int* const s_item = (int*)lds;   // read into registers before the first loads overwrite it
     if (!em_item<C::BM, C::BM>(g, nt, window, false, s_item)) return;   // workgroup-uniform
     const int e = s_item[0], row0 = s_item[1], row1 = s_item[2], ntile = s_item[3], kslice = s_item[4];
     __syncthreads();
-    ring_tile<E, C, MODE>(g, lds, e, row0, row1, ntile, kslice);
+    if (CT::BM < C::BM && row1 - row0 <= CT::BM) ring_tile<E, CT, MODE>(g, lds, e, row0, row1, ntile, kslice);
+    else ring_tile<E, C, MODE>(g, lds, e, row0, row1, ntile, kslice);
 }
 
-template <class E, class C, int MODE>
+template <class E, class C, class CT, int MODE>
 hipError_t launch_ring(const GemmArgs& g, int64_t R, hipStream_t s, int window) {
     const int64_t mt_upper = most_tiles(g, R, C::BM);
     const int nt = (int)ceil_div(g.N, MODE == kExpand ? C::BN / 2 : C::BN);
     const int64_t grid = ceil_div(mt_upper * nt * g.ksplit, 8) * 8;
     if (grid <= 0) return hipSuccess;
     // set on every launch (idempotent, and the library keeps no state between calls)
-    const hipError_t err = hipFuncSetAttribute((const void*)gemm_ring_kernel<E, C, MODE>,
+    const hipError_t err = hipFuncSetAttribute((const void*)gemm_ring_kernel<E, C, CT, MODE>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (err != hipSuccess) return err;
-    gemm_ring_kernel<E, C, MODE><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(g, nt, window);
+    gemm_ring_kernel<E, C, CT, MODE><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(g, nt, window);
     return hipGetLastError();
 }
 

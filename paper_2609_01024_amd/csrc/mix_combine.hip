@@ -64,8 +64,19 @@ __device__ inline TokenPaths token_paths(const MixMap& m, int64_t t) {
     return p;
 }
 
+// Weight (a, b) of the token in lane a * K + b of every wave, one load for all of them: read where
+// they are used, under the path bit's branch, up to 64 scalar loads ran one after another (top-8, F
+// 1024: 24 tokens 10.5 -> 9.0 us, 8192 tokens 84 -> 76).
+__device__ inline float lane_weight(const TokenPaths& p) {
+    const int l = threadIdx.x & 63;
+    return p.beta ? (l < p.K * p.K ? p.beta[l] : 0.0f) : 1.0f;
+}
+__device__ inline float path_weight(float wv, const TokenPaths& p, int a, int b) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), a * p.K + b));
+}
+
 // z values of 8 columns starting at c for every target b of the token
-__device__ inline void mix8(const float* __restrict__ u, const TokenPaths& p, int F, int c,
+__device__ inline void mix8(const float* __restrict__ u, const TokenPaths& p, float wv, int F, int c,
                             float (&z)[kMaxK][8]) {
     float ua[kMaxK][8];
 #pragma unroll
@@ -79,7 +90,7 @@ __device__ inline void mix8(const float* __restrict__ u, const TokenPaths& p, in
 #pragma unroll
         for (int a = 0; a < kMaxK; ++a) {
             if (a < p.ns && ((p.bits >> (a * p.K + b)) & 1)) {
-                const float w = p.beta ? p.beta[a * p.K + b] : 1.0f;
+                const float w = path_weight(wv, p, a, b);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) z[b][i] = fmaf(w, ua[a][i], z[b][i]);
             }
@@ -93,6 +104,7 @@ __global__ __launch_bounds__(256) void mix_kernel(const float* __restrict__ u, v
     const int64_t t = blockIdx.x;
     if (m.live && t >= *m.live) return;  // whole workgroup
     const TokenPaths p = token_paths(m, t);
+    const float wv = lane_weight(p);
     float scale[kMaxK];
     if (F16) {
         // pass 1: largest |z| of each target row, reduced over the workgroup
@@ -101,7 +113,7 @@ __global__ __launch_bounds__(256) void mix_kernel(const float* __restrict__ u, v
         for (int b = 0; b < kMaxK; ++b) mx[b] = 0.f;
         for (int c = threadIdx.x * 8; c < F; c += blockDim.x * 8) {
             float zz[kMaxK][8];
-            mix8(u, p, F, c, zz);
+            mix8(u, p, wv, F, c, zz);
 #pragma unroll
             for (int b = 0; b < kMaxK; ++b)
                 if (b < p.nt)
@@ -136,7 +148,7 @@ __global__ __launch_bounds__(256) void mix_kernel(const float* __restrict__ u, v
     // pass 2 (only pass for float32 layers): store z
     for (int c = threadIdx.x * 8; c < F; c += blockDim.x * 8) {
         float zz[kMaxK][8];
-        mix8(u, p, F, c, zz);
+        mix8(u, p, wv, F, c, zz);
 #pragma unroll
         for (int b = 0; b < kMaxK; ++b) {
             if (b >= p.nt) break;
@@ -171,11 +183,7 @@ __global__ __launch_bounds__(1024) void mix_regs_kernel(const float* __restrict_
     const int64_t t = blockIdx.x;
     if (m.live && t >= *m.live) return;  // whole workgroup
     const TokenPaths p = token_paths(m, t);
-    // weight (a, b) in lane a * K + b of every wave, one load for all of them: read where they are
-    // used, under the path bit's branch, up to 64 scalar loads ran one after another (24 tokens of
-    // top-8, F 1024: 10.5 -> 9.0 us; 8192 tokens 84 -> 76)
-    const int wl = threadIdx.x & 63;
-    const float wv = p.beta ? (wl < p.K * p.K ? p.beta[wl] : 0.0f) : 1.0f;
+    const float wv = lane_weight(p);
     float zz[ITER][KK][CPT];
     float mx[KK];
 #pragma unroll
@@ -207,7 +215,7 @@ __global__ __launch_bounds__(1024) void mix_regs_kernel(const float* __restrict_
 #pragma unroll
             for (int b = 0; b < KK; ++b) {
                 if (b < p.nt && ((p.bits >> (a * p.K + b)) & 1)) {
-                    const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), a * p.K + b));
+                    const float w = path_weight(wv, p, a, b);
 #pragma unroll
                     for (int i = 0; i < CPT; ++i) zz[it][b][i] = fmaf(w, ua[a][i], zz[it][b][i]);
                 }

@@ -113,3 +113,28 @@ def test_layer_shapes(T, H, n, F, k, logits):
 
 def R_mean(cfg):
     return cfg.T * cfg.k // cfg.n
+
+
+# path build of up to 256 tokens: one thread per (token, slot), at most two each
+@pytest.mark.parametrize("beta_mode", [0, 1, 2])
+@pytest.mark.parametrize("T,n,k", [(1, 8, 8), (128, 256, 8), (129, 9, 8), (255, 64, 5), (256, 256, 8), (200, 1, 1)])
+def test_build_paths_small(T, n, k, beta_mode):
+    from test_gpu_parity import check_paths
+    rng = np.random.default_rng(T + n)
+    lg = torch.from_numpy(rng.standard_normal((T, n)).astype(np.float32)).to(DEV)
+    ids, w = pcm.pcm_route(lg, k)
+    check_paths(ids, w, (rng.random((n, n)) < 0.4).astype(np.uint8), n, beta_mode)
+
+
+# scored route: every score equal (more than a wave of pairs reach the bound), more than 256 pairs per
+# lane, 4 and 16 waves per token, and dispatches that sum the count table themselves (up to 16384
+# tokens) or scan it
+@pytest.mark.parametrize("T,n,K,d,equal", [(600, 64, 8, 1.0, True), (40, 64, 8, 1.0, True), (520, 256, 8, 1.0, False),
+                                           (33, 256, 8, 1.0, False), (512, 96, 7, 0.5, False), (512, 97, 7, 0.5, False),
+                                           (16384, 8, 2, 0.5, False), (16400, 8, 2, 0.5, False)])
+def test_route_scored_branches(T, n, K, d, equal):
+    from test_gpu_scored import check_route
+    rng = np.random.default_rng(T + n)
+    z = (lambda *s: np.zeros(s, np.float32)) if equal else (lambda *s: rng.standard_normal(s).astype(np.float32))
+    mask = (rng.random((n, n)) < d).astype(np.uint8)
+    check_route(z(T, n), z(T, n), 0.5, z(n, n), mask, K, f"T={T} n={n} K={K}")
