@@ -62,7 +62,8 @@
 namespace pcm {
 namespace {
 
-// Find this workgroup's group and row range. Returns false past the last tile.
+// Find this workgroup's group and row range (s_tile: group, row0, row1, rows of the group). Returns
+// false past the last tile.
 template <int BM>
 __device__ bool find_tile(const int32_t* __restrict__ offsets, int n, int64_t a_rows, int64_t mt,
                           int* s_tile) {
@@ -71,6 +72,7 @@ __device__ bool find_tile(const int32_t* __restrict__ offsets, int n, int64_t a_
         s_tile[0] = 0;
         s_tile[1] = (int)(mt * BM);
         s_tile[2] = (int)min<int64_t>(a_rows, (mt + 1) * BM);
+        s_tile[3] = (int)a_rows;
         return true;
     }
     if (threadIdx.x < 64) {
@@ -93,6 +95,7 @@ __device__ bool find_tile(const int32_t* __restrict__ offsets, int n, int64_t a_
                 s_tile[0] = x;
                 s_tile[1] = r0;
                 s_tile[2] = min(lo[j] + rows[j], r0 + BM);
+                s_tile[3] = rows[j];
             }
             start += cnt[j];
         }
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(256) void widen_kernel(const uint16_t* __restrict__
 }
 
 // One tile of configuration C: rows [row0, row1) of group e, N tile ntile, K slice kslice.
-template <class C, int MODE>
+template <class C, int MODE, bool NT>
 __device__ __forceinline__ void il_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
                                         int ntile, int kslice) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -348,9 +351,11 @@ __device__ __forceinline__ void il_tile(const GemmArgs& g, char* lds, int e, int
     }
     // A stage i at lds + i * SA (i < 2), B stage i at lds + 2 * SA + i * SB (i < 3)
     auto load = [&](int q, int ksa, int ksb, char* abase, char* bbase) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(q < C::QA ? ra : (up[q] ? rb1 : rb0),
-                                                 (PCM_LDS void*)((q < C::QA ? abase : bbase) + dst[q]), 16, voff[q],
-                                                 (q < C::QA ? ksa : ksb) * 128, 0, 0);
+        if (q < C::QA)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (PCM_LDS void*)(abase + dst[q]), 16, voff[q], ksa * 128, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(up[q] ? rb1 : rb0, (PCM_LDS void*)(bbase + dst[q]), 16, voff[q],
+                                                     ksb * 128, 0, weight_policy(NT));
     };
     char* const A0 = lds;
     char* const B0 = lds + 2 * C::SA;
@@ -611,9 +616,10 @@ enum IlOrder { kGrouped = 0, kLongestFirst = 1, kExpertMajor = 2 };
 
 // order (an IlOrder): kLongestFirst is the order of il_item, kGrouped the grouped order of
 // tile_of, kExpertMajor the order of em_item (group_n is then the window).
+// once: weights_once.
 template <class C, class CT, int MODE>
 __global__ __launch_bounds__(C::NT) void gemm_il_kernel(GemmArgs g, int64_t mt_upper, int nt,
-                                                         int group_n, int order) {
+                                                         int group_n, int order, bool once) {
     // half of a tail tile (128 x 128 for the large tiles, each wave 64 x 64): the longest-first
     // order runs each tail item as two of these, so that shorter items fill the last round
     using CH = ICfg<CT::BM, C::BNB / 2, CT::WM, CT::WN>;
@@ -629,7 +635,7 @@ __global__ __launch_bounds__(C::NT) void gemm_il_kernel(GemmArgs g, int64_t mt_u
         const int half = s_item[6];
         __syncthreads();
         if (half) {                        // half of a tail item: N-tile of half width
-            il_tile<CH, MODE>(g, lds, e, row0, row1, ntile, kslice);
+            il_tile<CH, MODE, false>(g, lds, e, row0, row1, ntile, kslice);
             return;
         }
     } else if (order == kExpertMajor) {
@@ -645,10 +651,17 @@ __global__ __launch_bounds__(C::NT) void gemm_il_kernel(GemmArgs g, int64_t mt_u
         e = s_item[0], row0 = s_item[1], row1 = s_item[2];
         __syncthreads();
     }
-    if (row1 - row0 <= CT::BM)
-        il_tile<CT, MODE>(g, lds, e, row0, row1, ntile, kslice);
-    else
-        il_tile<C, MODE>(g, lds, e, row0, row1, ntile, kslice);
+    // the group's only row tile: its weights are read once (an accumulating projection has one group,
+    // and the two more tile bodies made it spill)
+    constexpr bool kOnce = base_mode(MODE) != kDownAccum;
+    const bool single = kOnce && once && g.offsets[e + 1] - g.offsets[e] <= C::BM;
+    if (row1 - row0 <= CT::BM) {
+        if (single) il_tile<CT, MODE, kOnce>(g, lds, e, row0, row1, ntile, kslice);
+        else il_tile<CT, MODE, false>(g, lds, e, row0, row1, ntile, kslice);
+    } else {
+        if (single) il_tile<C, MODE, kOnce>(g, lds, e, row0, row1, ntile, kslice);
+        else il_tile<C, MODE, false>(g, lds, e, row0, row1, ntile, kslice);
+    }
 }
 
 // --------------------------------------------------------------- staged kernel
@@ -673,7 +686,7 @@ template <class C, int MODE>
 __global__ __launch_bounds__(C::NT) void gemm_staged_kernel(GemmArgs g, int64_t mt_upper, int nt,
                                                             int group_n) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    __shared__ int s_tile[3];
+    __shared__ int s_tile[4];
     int64_t mt;
     int ntile;
     if (!tile_of(blockIdx.x, gridDim.x, mt_upper, nt, group_n, &mt, &ntile)) return;
@@ -775,7 +788,7 @@ template <int MODE, int NB, int SDP>
 __global__ __launch_bounds__(SWAVES * 64) void gemm_stream_kernel(GemmArgs g, int64_t mt_upper,
                                                                  int nt, int n_fastest) {
     static_assert(NB % 2 == 0 && (NB + 1) * (SDP - 1) <= 63, "gate/up halves; vmcnt range");
-    __shared__ int s_tile[3];
+    __shared__ int s_tile[4];
     const int64_t mt = n_fastest ? blockIdx.x / nt : blockIdx.x % mt_upper;
     const int ntile = n_fastest ? (int)(blockIdx.x % nt) : (int)(blockIdx.x / mt_upper);
     if (!find_tile<SROWS>(g.offsets, g.n, g.a_rows, mt, s_tile)) return;
@@ -919,7 +932,7 @@ __device__ inline void store_swiglu4(const GemmArgs& g, int r, int c, const floa
 }
 
 // Rows [row0, row1) of group e (at most 16 * MB), N tile ntile.
-template <int MODE, int NB, int MB, int D, int KW>
+template <int MODE, int NB, int MB, int D, int KW, bool NT>
 __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
                                              int ntile) {
     using C = LStream<MODE, NB, MB, D, KW>;
@@ -974,7 +987,7 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
             for (int h = 0; h < 2; ++h)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds((MODE == kExpand && b >= NB / 2) ? rb1 : rb0,
                                                          (PCM_LDS void*)(slot + b * 2048 + h * 1024), 16,
-                                                         voff[b][h], (first + p * KW) * 128, 0, 0);
+                                                         voff[b][h], (first + p * KW) * 128, 0, weight_policy(NT));
     };
     auto issue_a = [&](int j, int p) {
         char* slot = ring + j * C::kSlot;
@@ -1099,17 +1112,22 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
         }
 }
 
+// once: weights_once.
 template <int MODE, int NB, int MB, int D, int KW>
-__global__ __launch_bounds__(SWAVES * 64) void gemm_lstream_kernel(GemmArgs g, int64_t mt_upper, int nt) {
+__global__ __launch_bounds__(SWAVES * 64) void gemm_lstream_kernel(GemmArgs g, int64_t mt_upper, int nt,
+                                                                  bool once) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    __shared__ int s_tile[3];
+    __shared__ int s_tile[4];
     // the expansion runs a group's N tiles back to back (its gathered activation rows are then
     // shared through L2: 6% faster on the decode-shaped layer); the projection interleaves
     // the groups (4% faster than N tiles back to back there)
     const int64_t mt = MODE == kExpand ? blockIdx.x / nt : blockIdx.x % mt_upper;
     const int ntile = MODE == kExpand ? (int)(blockIdx.x % nt) : (int)(blockIdx.x / mt_upper);
     if (!find_tile<16 * MB>(g.offsets, g.n, g.a_rows, mt, s_tile)) return;
-    lstream_tile<MODE, NB, MB, D, KW>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
+    if (once && s_tile[3] <= 16 * MB)   // the group's only row tile
+        lstream_tile<MODE, NB, MB, D, KW, true>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
+    else
+        lstream_tile<MODE, NB, MB, D, KW, false>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
 }
 
 template <int MODE, int NB, int MB, int D, int KW = 1>
@@ -1123,7 +1141,8 @@ hipError_t launch_lstream_cfg(const GemmArgs& g, int64_t R, hipStream_t s) {
     const hipError_t err = hipFuncSetAttribute((const void*)gemm_lstream_kernel<MODE, NB, MB, D, KW>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (err != hipSuccess) return err;
-    gemm_lstream_kernel<MODE, NB, MB, D, KW><<<dim3((unsigned)grid), dim3(SWAVES * 64), C::kLds, s>>>(g, mt_upper, nt);
+    gemm_lstream_kernel<MODE, NB, MB, D, KW><<<dim3((unsigned)grid), dim3(SWAVES * 64), C::kLds, s>>>(
+        g, mt_upper, nt, weights_once(g, R, MODE));
     return hipGetLastError();
 }
 
@@ -1204,9 +1223,6 @@ hipError_t launch_stream(const GemmArgs& g, int64_t R, hipStream_t s, int depth)
 }
 
 // ---------------------------------------------------------------------- launch
-// A mean of fewer than 96 rows per group: most row tiles are tail tiles of at most 128 rows.
-inline bool mostly_tails(const GemmArgs& g, int64_t R) { return g.offsets && R < 96 * (int64_t)g.n; }
-
 template <class C, int MODE, bool IL, class CT = LargeIlTail>
 hipError_t launch_cfg(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTune& t) {
     // set on every launch (idempotent, and the library keeps no state between calls)
@@ -1258,7 +1274,7 @@ hipError_t launch_cfg(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTun
             grid = ceil_div(mt_upper * nt, 8) * 8 * g.ksplit;
         }
         gemm_il_kernel<C, CT, MODE><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(
-            g, mt_upper, nt, gparam, order);
+            g, mt_upper, nt, gparam, order, weights_once(g, R, MODE));
     } else {
         const int64_t grid = ceil_div(mt_upper * nt, 8) * 8 * g.ksplit;
         gemm_staged_kernel<C, MODE><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(g, mt_upper, nt, group_n);

@@ -22,6 +22,27 @@ inline int64_t most_tiles(const GemmArgs& g, int64_t R, int BM) {
     return (R + (BM - 1) * (R < g.n ? R : g.n)) / BM;
 }
 
+// Cache policy of a weight load: non-temporal where every weight is read once (weights_once).
+constexpr int weight_policy(bool nt) { return nt ? 2 : 0; }
+
+// Whether a grouped product's weights are worth reading non-temporally by the groups of a single row
+// tile, which read each of them once (the kernels check that): together they are more than half of the
+// 256 MB MALL, so that little of them is left there from the call before. A plain stream of 8 GB then reads at 7.1 TB/s instead of 6.2,
+// whatever the pattern (128 to 1024 bytes of a row, rows 2 to 28 KB apart). Decode shape, 32 tokens:
+// expansion 1548 -> 1376 us, projection 797 -> 717; Mixtral shape, 3 tokens 136 -> 126 and 87 -> 77; 40
+// tokens 312 -> 286 and 190 -> 173. Weights that stay in the MALL between calls are slower that way
+// (shared expert of 69 MB 31.1 -> 33.2 us, OLMoE shape, 1 token, projection 21.0 -> 22.6), as is a
+// second row tile (OLMoE shape, 100 tokens on 16-row tiles without that check, 73 -> 79 us).
+inline bool weights_once(const GemmArgs& g, int64_t R, int mode) {
+    const int64_t groups = R < g.n ? R : g.n;
+    // (from a mean of 512 rows on few groups are that small, and the check costs 0.3% of the fine-grained
+    // prefill)
+    return g.offsets && R < 512 * (int64_t)g.n && groups * g.N * g.K * (mode == kExpand ? 4 : 2) >= (int64_t(128) << 20);
+}
+
+// A mean of fewer than 96 rows per group: most row tiles are tail tiles of at most 128 rows.
+inline bool mostly_tails(const GemmArgs& g, int64_t R) { return g.offsets && R < 96 * (int64_t)g.n; }
+
 // First row and row count of groups 4 * lane .. 4 * lane + 3 (0 rows past n; without offsets one group
 // of a_rows rows). The five offsets are loaded without branches and waited for once: behind the bounds
 // check of each group they were four loads one after another, 1.5 us of every workgroup's start.

@@ -37,7 +37,7 @@ __device__ __forceinline__ void ring_barrier() {
 // lane's address of load q (A rows for q < QA, then B rows) in the first slice: row
 // (q' * NW + wave) * 8 + lane / 8 of its part, chunk (lane % 8) ^ ((row >> 1) & 7). KT barriers.
 // E: the element type (SIZE bytes, NJ MFMA steps per chunk, fragment reads, step).
-template <class E, class C>
+template <class E, class C, bool NT = false>
 __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, char* lds,
                                           floatx4 (&acc)[C::NBK][C::MB]) {
     const int lane = threadIdx.x & 63;
@@ -47,9 +47,13 @@ __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, ch
 #pragma unroll
         for (int q = 0; q < C::LPW; ++q) {
             const int blk = (q < C::QA ? q : q - C::QA) * C::NW + wave;
-            __builtin_amdgcn_global_load_lds((const PCM_GLOBAL void*)src[q],
-                                             (PCM_LDS void*)(lds + slot * C::SLICE + (q < C::QA ? 0 : C::SA) + blk * 1024),
-                                             16, 0, 0);
+            if (q < C::QA)
+                __builtin_amdgcn_global_load_lds((const PCM_GLOBAL void*)src[q],
+                                                 (PCM_LDS void*)(lds + slot * C::SLICE + blk * 1024), 16, 0, 0);
+            else
+                __builtin_amdgcn_global_load_lds((const PCM_GLOBAL void*)src[q],
+                                                 (PCM_LDS void*)(lds + slot * C::SLICE + C::SA + blk * 1024), 16, 0,
+                                                 weight_policy(NT));
             src[q] += 128;
         }
     };
@@ -94,7 +98,7 @@ __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, ch
 }
 
 // One tile: rows [row0, row1) of group e, N tile ntile, K slice kslice of g.ksplit.
-template <class E, class C, int MODE>
+template <class E, class C, int MODE, bool NT>
 __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
                                           int ntile, int kslice) {
     static_assert(C::WTN % 32 == 0, "gate/up halves");
@@ -126,7 +130,7 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
         src[q] = base + (int64_t)kslice * KT * 128 + chunk * 16;
     }
     floatx4 acc[C::NBK][C::MB];
-    ring_loop<E, C>(src, KT, lds, acc);
+    ring_loop<E, C, NT>(src, KT, lds, acc);
     GemmArgs gs = g;
     if (kslice) gs.out = (float*)g.out + (int64_t)kslice * g.rows_total * N;
     epilogue<MODE, C::MB, C::NBK, C::WTM, C::WTN, kOutCols, typename E::Silu>(gs, acc, row0, row1, ntile, wave / C::WN,
@@ -136,16 +140,24 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, char* lds, int e, i
 // Workgroups walk the expert-major order of em_item with the window `window`. A group's last tile with
 // at most CT::BM rows runs as the smaller tile CT (the same columns), sparing the loads of padding
 // rows (bf16, one group of 150 rows, H 2048, F 5632: three kernels 47.2 -> 38.5 us; CT = C: none).
+// once: weights_once.
 template <class E, class C, class CT, int MODE>
-__global__ __launch_bounds__(C::NT) void gemm_ring_kernel(GemmArgs g, int nt, int window) {
+__global__ __launch_bounds__(C::NT) void gemm_ring_kernel(GemmArgs g, int nt, int window, bool once) {
     static_assert(CT::NT == C::NT && CT::BN == C::BN && CT::BM <= C::BM && CT::LDS_BYTES <= C::LDS_BYTES, "tail tile");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     int* const s_item = (int*)lds;   // read into registers before the first loads overwrite it
     if (!em_item<C::BM, C::BM>(g, nt, window, false, s_item)) return;   // workgroup-uniform
     const int e = s_item[0], row0 = s_item[1], row1 = s_item[2], ntile = s_item[3], kslice = s_item[4];
     __syncthreads();
-    if (CT::BM < C::BM && row1 - row0 <= CT::BM) ring_tile<E, CT, MODE>(g, lds, e, row0, row1, ntile, kslice);
-    else ring_tile<E, C, MODE>(g, lds, e, row0, row1, ntile, kslice);
+    // the group's only row tile: its weights are read once (bf16 layers; float32 ones are small)
+    const bool single = E::SIZE == 2 && once && g.offsets[e + 1] - g.offsets[e] <= C::BM;
+    if (CT::BM < C::BM && row1 - row0 <= CT::BM) {
+        if (single) ring_tile<E, CT, MODE, E::SIZE == 2>(g, lds, e, row0, row1, ntile, kslice);
+        else ring_tile<E, CT, MODE, false>(g, lds, e, row0, row1, ntile, kslice);
+    } else {
+        if (single) ring_tile<E, C, MODE, E::SIZE == 2>(g, lds, e, row0, row1, ntile, kslice);
+        else ring_tile<E, C, MODE, false>(g, lds, e, row0, row1, ntile, kslice);
+    }
 }
 
 template <class E, class C, class CT, int MODE>
@@ -158,7 +170,8 @@ hipError_t launch_ring(const GemmArgs& g, int64_t R, hipStream_t s, int window) 
     const hipError_t err = hipFuncSetAttribute((const void*)gemm_ring_kernel<E, C, CT, MODE>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (err != hipSuccess) return err;
-    gemm_ring_kernel<E, C, CT, MODE><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(g, nt, window);
+    gemm_ring_kernel<E, C, CT, MODE><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(g, nt, window,
+        weights_once(g, R, MODE));
     return hipGetLastError();
 }
 
