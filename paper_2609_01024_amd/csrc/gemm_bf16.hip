@@ -1168,9 +1168,9 @@ inline bool offsets_reach(const GemmArgs& g) {
 
 // The streaming kernels that split K over a workgroup's waves (KW = 4). One group of rows: every
 // output column block has few workgroups (2048 columns: 64 of 32), so each takes up to 64 rows at
-// once, and the projection 16 columns per workgroup. Shared expert, H 2048, F 5632, three kernels:
-// 1 row 55.9 -> 23.2 us, 16 rows 83.1 -> 25.6, 48 rows 85.2 -> 35.0, 64 rows 87.3 -> 39.0 (the
-// large tiles from 16 rows on before, 8 to 44 workgroups).
+// once, and the projection 16 columns per workgroup. Shared expert, H 2048, F 5632, three kernels,
+// cold weights: 1 row 55.9 -> 20.7 us, 48 rows 85.2 -> 25.8, 64 rows 87.3 -> 27.5 (the large tiles
+// from 16 rows on before, 8 to 44 workgroups).
 //
 // 16-column blocks per workgroup: one, or two where one makes more workgroups than there are compute
 // units (the activations are then fetched half as often: 48 rows, H 2048, F 5632, the three kernels
@@ -1178,18 +1178,32 @@ inline bool offsets_reach(const GemmArgs& g) {
 inline int one_group_blocks(const GemmArgs& g, int64_t R) {
     return ceil_div(R, 64) * ceil_div(g.N, 16) > 256 ? 2 : 1;
 }
+// 16-row blocks per workgroup where it takes one column block: the fewest that leave no more
+// workgroups than compute units. A workgroup fetches its rows' activations whole, at most 54 GB/s to
+// a compute unit, so where columns alone leave units idle the rows are split over them too (H 2048,
+// F 5632, the three kernels, cold weights: 32 rows 26.3 -> 23.4 us, 64 rows 33.3 -> 27.5; past 256
+// workgroups, H 3072 and F 8192, the split loses: 64 rows 49.0 -> 53.1).
+inline int one_group_row_blocks(const GemmArgs& g, int64_t R) {
+    for (int m = 1; m < 4; ++m)
+        if (ceil_div(R, 16 * m) * ceil_div(g.N, 16) <= 256) return m;
+    return (int)std::min<int64_t>(4, ceil_div(R, 16));
+}
 template <int MODE>
 hipError_t launch_stream_ksplit(const GemmArgs& g, int64_t R, hipStream_t s) {
     if (!g.offsets) {
         constexpr int E = MODE == kExpand ? 2 : 1;   // weight blocks of 16 output columns
-        auto go = [&](auto nb) {
-            constexpr int NB = decltype(nb)::value;
-            if (R <= 16) return launch_lstream_cfg<MODE, NB, 1, 3, 4>(g, R, s);
-            if (R <= 32) return launch_lstream_cfg<MODE, NB, 2, 2, 4>(g, R, s);
-            if (R <= 48) return launch_lstream_cfg<MODE, NB, 3, 2, 4>(g, R, s);
-            return launch_lstream_cfg<MODE, NB, 4, 2, 4>(g, R, s);
-        };
-        return one_group_blocks(g, R) == 2 ? go(std::integral_constant<int, 2 * E>()) : go(std::integral_constant<int, E>());
+        if (one_group_blocks(g, R) == 2) {
+            if (R <= 16) return launch_lstream_cfg<MODE, 2 * E, 1, 3, 4>(g, R, s);
+            if (R <= 32) return launch_lstream_cfg<MODE, 2 * E, 2, 2, 4>(g, R, s);
+            if (R <= 48) return launch_lstream_cfg<MODE, 2 * E, 3, 2, 4>(g, R, s);
+            return launch_lstream_cfg<MODE, 2 * E, 4, 2, 4>(g, R, s);
+        }
+        switch (one_group_row_blocks(g, R)) {
+            case 1: return launch_lstream_cfg<MODE, E, 1, 3, 4>(g, R, s);
+            case 2: return launch_lstream_cfg<MODE, E, 2, 3, 4>(g, R, s);
+            case 3: return launch_lstream_cfg<MODE, E, 3, 2, 4>(g, R, s);
+            default: return launch_lstream_cfg<MODE, E, 4, 2, 4>(g, R, s);
+        }
     }
     // 32 rows per tile from a mean of 4 rows on, where groups of more than 16 become common (40
     // tokens on the Mixtral shape: expansion 339 -> 311 us, projection 210 -> 188; below, 0-2% slower)
@@ -1338,7 +1352,7 @@ using RingNarrowTail = RCfg<32, 64, 2, 2, 4>;
 // RingWide 24 KB and 0.42-0.48 us, RingNarrow 16 KB and 0.26-0.37 us, streaming 10-12 KB and
 // 0.15-0.22 us), so smaller tiles move more bytes per output but spread over more compute units. The
 // times below are those rates over 256 compute units (shared expert, H 2048, F 5632, expansion and
-// projection in us, L / R / N / S: 64 rows 29 49 / 19 45 / 16 34 / 19 17; 256 rows 43 106 / 29 44 /
+// projection in us, L / R / N / S: 64 rows 29 49 / 19 45 / 16 34 / 19 11; 256 rows 43 106 / 29 44 /
 // 28 34 / 46 31; 1000 rows 52 102 / 73 45 / 82 48 / 145 102; 4096 rows 147 107 / 271 159 / 398 220 /
 // 563 415). The smaller tiles are taken where they come out a fifth faster. Groups of fewer than 40
 // rows on average are bound by their weights, and one 64-row tile wastes least (OLMoE shape, 256

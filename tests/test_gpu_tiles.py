@@ -61,10 +61,10 @@ def test_router_forms(T, H, n, k):
 
 
 # one group of rows (the shared expert) on the shapes that pick_shape chooses between: streaming with
-# the K split (rows 1 to 64 per tile, 17 and 33 and 49 start another block), 64-row ring tiles (row and
+# the K split (rows 1 to 64 per tile, 17 and 33 and 49 start another block; several row tiles where N is small), 64-row ring tiles (row and
 # column remainders), large tiles; K = 512 and 448 are the two sides of the split's line
 @pytest.mark.parametrize("T,H,Fs", [(1, 512, 512), (16, 448, 576), (17, 576, 1088), (33, 1024, 640), (49, 1024, 1600),
-                                    (64, 2048, 512), (65, 2048, 512), (128, 1024, 1984), (300, 1024, 2112),
+                                    (64, 2048, 512), (40, 2112, 2176), (64, 2112, 2176), (65, 2048, 512), (128, 1024, 1984), (300, 1024, 2112),
                                     (1000, 576, 2048), (2500, 320, 320)])
 def test_dense_swiglu_shapes(T, H, Fs):
     cfg = scaled(CONFIGS["finegrained_shared"], T=T, H=H, F=64, shared_F=Fs, name=f"dense{T}")
