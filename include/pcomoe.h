@@ -314,12 +314,12 @@ pcm_status pcm_project_combine_scored(pcm_dtype dtype, const void* u, const void
  * forces kernel choices the library otherwise makes by shape (every choice computes the same
  * bits, but for the splits of K: the large tiles' projection slices, and the streaming kernel's
  * default ring, which adds four partial sums where rows are few and K is long) and that records
- * HIP events between the internal stages of a call; tuning = NULL is the plain call. They let tests check each kernel on the same inputs and let benchmarks time
- * each stage on the stream it runs on. Values outside the documented sets give PCM_ERR_ARG. */
+ * HIP events between the internal stages of a call; tuning = NULL is the plain call. They let
+ * tests check each kernel on the same inputs and let benchmarks time each stage on the stream it
+ * runs on. Values outside the documented sets give PCM_ERR_ARG. */
 typedef struct pcm_tuning {
-    int tile;              /* 0: chosen by the shape (smaller tiles of 64 rows among the choices);
-                              'S' the few-row streaming
-                              kernel, 'M' the medium tiles, 'L' the large tiles on four waves,
+    int tile;              /* 0: chosen by the shape (smaller tiles of 64 rows among the choices); 'S' the few-row
+                              streaming kernel, 'M' the medium tiles, 'L' the large tiles on four waves,
                               'W' the large tiles on eight waves (two per SIMD; the default
                               for an expansion that takes the large tiles); for 'L' and 'W'
                               the medium tiles run instead where 32-bit buffer offsets would
