@@ -17,7 +17,7 @@ DEV = "cuda"
 # float32: 64 x 64 tiles from 768 expected tiles on, 32 x 64 below; K slices of 32 values
 @pytest.mark.parametrize("T,H,n,F,k", [(1, 64, 1, 64, 1), (31, 64, 1, 192, 1), (33, 128, 3, 64, 2),
                                        (130, 192, 5, 448, 3), (700, 320, 6, 2112, 4),
-                                       (64, 4160, 32, 1024, 8)])
+                                       (64, 4160, 32, 1024, 8), (9, 64, 12, 1088, 8)])
 def test_f32_layer_tiles(T, H, n, F, k):
     cfg = scaled(CONFIGS["tiny"], T=T, H=H, n=n, F=F, k=k, x_std=1.0, logits="normal", name=f"f32_{T}_{H}")
     say(f"float32 tiles {cfg.name}")
@@ -85,12 +85,14 @@ def test_dense_swiglu_shapes(T, H, Fs):
 
 
 # grouped rows: the streaming K split (below 16 rows per expert; 16-row tiles, 32-row from a mean of
-# 4 on, several tiles in one expert), ring tiles, and a K split of the projection on the ring
+# 4 on, several tiles in one expert), ring tiles, and a K split of the projection on the ring; the last
+# three: top-8 mixes whose last wave has few columns (path weights are read from lanes past them)
 @pytest.mark.parametrize("T,H,n,F,k,logits", [(1, 1024, 64, 2048, 8, "normal"), (3, 4096, 8, 2112, 2, "normal"),
                                               (40, 1024, 8, 2048, 2, "normal+one_expert"),
                                               (200, 1088, 60, 2048, 4, "zipf"), (130, 512, 16, 576, 4, "zipf"),
                                               (70, 320, 4, 4096, 1, "normal"), (257, 192, 5, 1088, 2, "normal"),
-                                              (900, 256, 3, 1536, 2, "normal")])
+                                              (900, 256, 3, 1536, 2, "normal"), (5, 128, 16, 1088, 8, "normal"),
+                                              (7, 64, 10, 4160, 8, "normal"), (6, 64, 9, 8256, 8, "normal")])
 def test_layer_shapes(T, H, n, F, k, logits):
     cfg = scaled(CONFIGS["olmoe"], T=T, H=H, n=n, F=F, k=k, logits=logits, zipf_s=1.1, name=f"shape{T}_{H}")
     say(f"layer shapes {cfg.name}")
