@@ -66,10 +66,13 @@ __device__ inline TokenPaths token_paths(const MixMap& m, int64_t t) {
 
 // Weight (a, b) of the token in lane a * K + b of every wave, one load for all of them: read where
 // they are used, under the path bit's branch, up to 64 scalar loads ran one after another (top-8, F
-// 1024: 24 tokens 10.5 -> 9.0 us, 8192 tokens 84 -> 76).
+// 1024: 24 tokens 10.5 -> 9.0 us, 8192 tokens 84 -> 76). The empty asm keeps the load here, where every
+// lane is active: moved under a column bound, the lanes past the last column would not hold their weights.
 __device__ inline float lane_weight(const TokenPaths& p) {
     const int l = threadIdx.x & 63;
-    return p.beta ? (l < p.K * p.K ? p.beta[l] : 0.0f) : 1.0f;
+    float v = p.beta ? (l < p.K * p.K ? p.beta[l] : 0.0f) : 1.0f;
+    asm volatile("" : "+v"(v));
+    return v;
 }
 __device__ inline float path_weight(float wv, const TokenPaths& p, int a, int b) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), a * p.K + b));
