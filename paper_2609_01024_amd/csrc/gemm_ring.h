@@ -37,9 +37,10 @@ __device__ __forceinline__ void ring_barrier() {
 // lane's address of load q (A rows for q < QA, then B rows) in the first slice: row
 // (q' * NW + wave) * 8 + lane / 8 of its part, chunk (lane % 8) ^ ((row >> 1) & 7). KT barriers.
 // E: the element type (SIZE bytes, NJ MFMA steps per chunk, fragment reads, step).
-template <class E, class C, bool NT = false>
+// FOLD: the sums of every `fold` (>= 1) slices are added to a total instead of running on.
+template <class E, class C, bool NT = false, bool FOLD = false>
 __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, char* lds,
-                                          floatx4 (&acc)[C::NBK][C::MB]) {
+                                          floatx4 (&acc)[C::NBK][C::MB], int fold = 0) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / C::WN, wn = wave % C::WN;
@@ -61,6 +62,13 @@ __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, ch
     for (int nb = 0; nb < C::NBK; ++nb)
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb) acc[nb][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 total[C::NBK][C::MB];
+    int left = fold;
+    if constexpr (FOLD)
+#pragma unroll
+        for (int nb = 0; nb < C::NBK; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb) total[nb][mb] = acc[nb][mb];
     const int r16 = lane & 15, kg = lane >> 4;
 #pragma unroll
     for (int s = 0; s < C::NS - 1; ++s)
@@ -93,8 +101,24 @@ __device__ __forceinline__ void ring_loop(const char* (&src)[C::LPW], int KT, ch
 #pragma unroll
                         for (int mb = 0; mb < C::MB; ++mb) acc[nb][mb] = E::step(st, bf[nb], af[mb], acc[nb][mb]);
             }
+            if constexpr (FOLD)
+                if (--left == 0) {   // uniform
+                    left = fold;
+#pragma unroll
+                    for (int nb = 0; nb < C::NBK; ++nb)
+#pragma unroll
+                        for (int mb = 0; mb < C::MB; ++mb) {
+                            total[nb][mb] += acc[nb][mb];
+                            acc[nb][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        }
+                }
         }
     }
+    if constexpr (FOLD)
+#pragma unroll
+        for (int nb = 0; nb < C::NBK; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb) acc[nb][mb] += total[nb][mb];
 }
 
 // One tile: rows [row0, row1) of group e, N tile ntile, K slice kslice of g.ksplit.

@@ -3,6 +3,9 @@
 // four logits as 64-bit keys (order-preserving float bits, then the complemented expert
 // id), so a wave-wide maximum picks the largest logit and, among equal logits, the lower
 // id. k rounds of the maximum give the slots in order.
+#include <algorithm>
+#include <cmath>
+
 #include "gemm_ring.h"
 
 namespace pcm {
@@ -481,7 +484,8 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
 //    and the experts' rows (4 to 12 slices in LDS, so that most of a compute unit's 64 bytes per
 //    clock stay requested), the logits go through LDS, and sixteen waves run the top-k of two
 //    tokens each. x is read once; the router weights come from L2. 8192 tokens, H 2048, 64
-//    experts: 39.0 -> 13.4 us; 16384 tokens, H 7168, 256 experts: 830 -> 158 us.
+//    experts: 39.0 -> 14.5 us (13.4 without the folds); 16384 tokens, H 7168, 256 experts, without
+//    the folds: 830 -> 158 us.
 //  * router_part_kernel, then router_topk_kernel: a workgroup computes one 16-expert x 16-token
 //    block over one K slice, its four waves splitting the slice and adding through LDS;
 //    part[s][t][e]. Then one wave per token adds the slices, all loaded at once, and runs the
@@ -503,7 +507,7 @@ struct ElemRouter {   // bf16 x bf16, the router rows as the first operand
 template <class C>
 __device__ __forceinline__ void router_fused_body(char* lds, const uint16_t* __restrict__ x,
                                                   const uint16_t* __restrict__ wr, int64_t T, int H,
-                                                  int n, int k, float* __restrict__ logits,
+                                                  int n, int k, int fold, float* __restrict__ logits,
                                                   int32_t* __restrict__ ids, float* __restrict__ w) {
     constexpr int EPL = C::BN / 64;
     constexpr int ROW = EPL * 64 + 4;   // floats of a padded LDS row of logits
@@ -520,7 +524,7 @@ __device__ __forceinline__ void router_fused_body(char* lds, const uint16_t* __r
             const int64_t row = q < C::QA ? min<int64_t>(t0 + lr, T - 1) : min(lr, n - 1);
             src[q] = (const char*)((q < C::QA ? x : wr) + row * H) + ((lane & 7) ^ ((lr >> 1) & 7)) * 16;
         }
-        ring_loop<ElemRouter, C>(src, KT, lds, acc);
+        ring_loop<ElemRouter, C, false, true>(src, KT, lds, acc, fold);
     } else {
         for (int kt = 0; kt < KT; ++kt) ring_barrier();   // the loop's barriers
     }
@@ -558,12 +562,12 @@ __device__ __forceinline__ void router_fused_body(char* lds, const uint16_t* __r
 template <class C>
 __global__ __launch_bounds__(1024) void router_fused_kernel(const uint16_t* __restrict__ x,
                                                             const uint16_t* __restrict__ wr,
-                                                            int64_t T, int H, int n, int k,
+                                                            int64_t T, int H, int n, int k, int fold,
                                                             float* __restrict__ logits,
                                                             int32_t* __restrict__ ids,
                                                             float* __restrict__ w) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    router_fused_body<C>(lds, x, wr, T, H, n, k, logits, ids, w);
+    router_fused_body<C>(lds, x, wr, T, H, n, k, fold, logits, ids, w);
 }
 
 __global__ __launch_bounds__(256) void router_part_kernel(const uint16_t* __restrict__ x,
@@ -746,15 +750,21 @@ hipError_t launch_router_fused(const uint16_t* x, const uint16_t* wr, int64_t T,
     const hipError_t err = hipFuncSetAttribute((const void*)router_fused_kernel<C>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
     if (err != hipSuccess) return err;
-    router_fused_kernel<C><<<(unsigned)ceil_div(T, kRouterTok), 1024, C::LDS_BYTES, s>>>(x, wr, T, H, n, k, logits,
-                                                                                        ids, w);
+    // One chain of additions over all of H has twice the rounding error of the slices' sums (2018
+    // tokens, H 6528, 181 experts: weights off by 1.4e-6 against 7.4e-7), so the sums are folded; chains
+    // of about sqrt(H / 32) MFMA steps (two to a 64-wide slice) leave the least: 2.6e-7 there, and
+    // 1.3e-7 against 3.9e-7 at 8192 tokens, H 2048, 64 experts. The folds take 8%: 44.9 -> 48.3 us
+    // (two launches 73.0) and 13.4 -> 14.5 (39.0).
+    const int fold = std::max(1, (int)(0.5 * std::sqrt(H / 32.0) + 0.5));
+    router_fused_kernel<C><<<(unsigned)ceil_div(T, kRouterTok), 1024, C::LDS_BYTES, s>>>(x, wr, T, H, n, k, fold,
+                                                                                        logits, ids, w);
     return hipGetLastError();
 }
 
 // Whether the one-launch router is the faster one. Its workgroups take the bytes of 32 tokens and
 // of every expert (in 64s) at about 65 GB/s each, one workgroup on each of 256 compute units at a
 // time; the two launches move 32 rows per 16 x 16 block at about 9 TB/s in all, 138 times as much
-// (both with 5-6 us besides; H 2048, 64 experts: 1024 tokens 11.2 against 9.4 us, 2048 tokens 11.5
+// (both with 5-6 us besides; without the folds, which add up to 8%, H 2048, 64 experts: 1024 tokens 11.2 against 9.4 us, 2048 tokens 11.5
 // against 13.4, 8192 tokens 13.4 against 36.6; H 7168, 256 experts: 1024 tokens 65.6 against 56.4,
 // 2048 tokens 65.9 against 105). With at most 32 experts half of its expert rows would be padding
 // (8 experts, H 4096, 8192 tokens: 21.3 against 19.4 us).

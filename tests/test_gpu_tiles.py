@@ -60,6 +60,32 @@ def test_router_forms(T, H, n, k):
     check_route_logits(x, wr, k, f"T={T} H={H} n={n} k={k}")
 
 
+# The one-launch router folds its sums every few K slices, so its rounding error against 64 bits stays at
+# that of the two launches, which add partial sums of K slices (chains of 51 MFMA steps at H 6528, 1000
+# tokens: error about sqrt(51 / 2); folded, chains of 14 steps and 15 of them, sqrt(14 / 2 + 15 / 2); one
+# chain of 204 steps would show twice the two launches' error). A quarter is left for the sample. H = 256
+# and 320: one slice per chain, the fewest.
+@pytest.mark.parametrize("T,H,n", [(2018, 6528, 181), (2400, 4096, 64), (4129, 320, 100), (4129, 256, 256)])
+def test_router_fold_error(T, H, n):
+    say(f"router fold T={T} H={H} n={n}")
+    g = torch.Generator().manual_seed(H)
+    x = torch.randn((T, H), generator=g).to(torch.bfloat16)
+    wr = (torch.randn((n, H), generator=g) * 0.02).to(torch.bfloat16)
+    ref = x.double() @ wr.double().T
+    xd, wd = x.to(DEV), wr.to(DEV)
+    one = pcm.pcm_route_logits(xd, wd, 1, want_logits=True)[2]
+    two = pcm.pcm_route_logits(xd[:1000].contiguous(), wd, 1, want_logits=True)[2]
+    torch.cuda.synchronize()
+
+    def error(lg):
+        r = ref[:lg.shape[0]]
+        return float((lg.cpu().double() - r).norm() / r.norm())
+    e1, e2 = error(one), error(two)
+    print(f"  one launch {e1:.2e}, two {e2:.2e}", flush=True)
+    # (24 bits: results that are all exact up to their last rounding leave 2^-24 / sqrt(3))
+    assert e1 <= max(1.25 * e2, 2.0 ** -24), (e1, e2)
+
+
 # one group of rows (the shared expert) on the shapes that pick_shape chooses between: streaming with
 # the K split (rows 1 to 64 per tile, 17 and 33 and 49 start another block; several row tiles where N is small), 64-row ring tiles (row and
 # column remainders), large tiles; K = 512 and 448 are the two sides of the split's line
