@@ -5,6 +5,7 @@
 // id. k rounds of the maximum give the slots in order.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "gemm_ring.h"
 
@@ -486,13 +487,14 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
 //    tokens each. x is read once; the router weights come from L2. 8192 tokens, H 2048, 64
 //    experts: 39.0 -> 14.5 us (13.4 without the folds); 16384 tokens, H 7168, 256 experts, without
 //    the folds: 830 -> 158 us.
-//  * router_part_kernel, then router_topk_kernel: a workgroup computes one 16-expert x 16-token
-//    block over one K slice, its four waves splitting the slice and adding through LDS;
-//    part[s][t][e]. Then one wave per token adds the slices, all loaded at once, and runs the
-//    top-k. A few tokens then still use many compute units. (24 tokens, H 2048, 64 experts: 9.4 ->
-//    6.0 us; with a wave per K slice, the top-k kernel added up to 64 slices in eight rounds of
-//    loads.)
-constexpr int kRouterTok = 32, kRouterSlices = 16;
+//  * router_part_kernel, then router_topk_kernel: a wave computes one 16-expert x 16-token block of
+//    partial dot products over one K slice (router_split: about 2048 waves share the work, so that a
+//    few tokens still use many compute units), fragments loaded straight from global memory;
+//    part[t][s][e]. Then one workgroup per token adds the slices in ascending order, all loaded at once,
+//    and runs the top-k (eight slices at a time before: 24 tokens, H 2048, 64 experts 9.6 -> 6.9 us; a
+//    workgroup's waves adding their slices to 16 sums before that took 6.2, in another order of the
+//    sums: a logit that moves in its last bit can send a later layer's near-tie to another expert).
+constexpr int kRouterTok = 32;
 
 struct ElemRouter {   // bf16 x bf16, the router rows as the first operand
     static constexpr int SIZE = 2, NJ = 1;
@@ -573,11 +575,11 @@ __global__ __launch_bounds__(1024) void router_fused_kernel(const uint16_t* __re
 __global__ __launch_bounds__(256) void router_part_kernel(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ wr,
                                                           int64_t T, int H, int n, int et,
-                                                          int64_t tt, int steps,
+                                                          int64_t tt, int ks, int steps,
                                                           float* __restrict__ part) {
-    __shared__ floatx4 red[3][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t unit = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int64_t unit = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (unit >= (int64_t)et * tt * ks) return;  // wave-uniform
     const int e_tile = (int)(unit % et);
     const int64_t t_tile = (unit / et) % tt;
     const int s = (int)(unit / ((int64_t)et * tt));
@@ -585,51 +587,109 @@ __global__ __launch_bounds__(256) void router_part_kernel(const uint16_t* __rest
     const int64_t t0 = t_tile * 16;
     const int64_t tok = t0 + r16 < T ? t0 + r16 : T - 1;
     const int e = e_tile * 16 + r16 < n ? e_tile * 16 + r16 : n - 1;
-    const int KT = H / 32, k0 = (s * 4 + wave) * steps, k1 = k0 + steps < KT ? k0 + steps : KT;
+    const int KT = H / 32, k0 = s * steps, k1 = k0 + steps < KT ? k0 + steps : KT;
     const bf16x8* xp = (const bf16x8*)(x + tok * H + kg * 8);
     const bf16x8* wp = (const bf16x8*)(wr + (int64_t)e * H + kg * 8);
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int kt = k0; kt < k1; ++kt)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[kt * 4], xp[kt * 4], acc, 0, 0, 0);
-    if (wave) red[wave - 1][lane] = acc;
-    __syncthreads();
-    if (wave) return;
+    int kt = k0;
+    auto chunk = [&](auto c) {   // c steps' fragments loaded at once
+        constexpr int U = decltype(c)::value;
+        bf16x8 wf[U], xf[U];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc += red[q][lane];
+        for (int j = 0; j < U; ++j) {
+            wf[j] = wp[(kt + j) * 4];
+            xf[j] = xp[(kt + j) * 4];
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[j], acc, 0, 0, 0);
+        kt += U;
+    };
+    while (kt + 8 <= k1) chunk(std::integral_constant<int, 8>());
+    if (kt + 4 <= k1) chunk(std::integral_constant<int, 4>());
+    if (kt + 2 <= k1) chunk(std::integral_constant<int, 2>());
+    if (kt < k1) chunk(std::integral_constant<int, 1>());
     // acc[r]: expert e_tile*16 + 4*kg + r of token t0 + r16
     const int npad = et * 16;
     if (t0 + r16 < T)
-        *(floatx4*)(part + ((int64_t)s * T + t0 + r16) * npad + e_tile * 16 + 4 * kg) = acc;
+        *(floatx4*)(part + ((t0 + r16) * ks + s) * npad + e_tile * 16 + 4 * kg) = acc;
 }
 
-template <int EPL>
-__global__ __launch_bounds__(64) void router_topk_kernel(const float* __restrict__ part, int64_t T,
-                                                         int n, int npad, int ks, int k,
-                                                         float* __restrict__ logits,
+// Few slices: one wave per token, CH (at least ks) slices of its experts loaded at once, added in order.
+template <int EPL, int CH>
+__global__ __launch_bounds__(64) void router_topk_kernel(const float* __restrict__ part, int n, int npad,
+                                                         int ks, int k, float* __restrict__ logits,
                                                          int32_t* __restrict__ ids,
                                                          float* __restrict__ w) {
     const int lane = threadIdx.x;
     const int64_t t = blockIdx.x;
-    float v[EPL][kRouterSlices];   // every slice loaded before the first sum
+    const float* const p = part + t * ks * npad;
+    float v[EPL][CH];
 #pragma unroll
     for (int q = 0; q < EPL; ++q)
 #pragma unroll
-        for (int s = 0; s < kRouterSlices; ++s)
-            v[q][s] = (s < ks && lane + 64 * q < npad) ? part[((int64_t)s * T + t) * npad + lane + 64 * q] : 0.0f;
+        for (int s = 0; s < CH; ++s)
+            v[q][s] = (s < ks && lane + 64 * q < npad) ? p[s * npad + lane + 64 * q] : 0.0f;
     float lv[EPL];
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
-        lv[q] = v[q][0];
+        lv[q] = 0.0f;
 #pragma unroll
-        for (int s = 1; s < kRouterSlices; ++s) lv[q] += v[q][s];
+        for (int s = 0; s < CH; ++s) lv[q] += v[q][s];
         if (logits && lane + 64 * q < n) logits[t * n + lane + 64 * q] = lv[q];
     }
-    float p;
-    const int e = select_token<EPL>(lv, n, k, lane, &p);
+    float p_;
+    const int e = select_token<EPL>(lv, n, k, lane, &p_);
     if (lane < k) {
         ids[t * k + lane] = e;
-        w[t * k + lane] = p;
+        w[t * k + lane] = p_;
+    }
+}
+
+// Many slices (few tokens): one workgroup per token loads up to 64 KB of them at once, 16 bytes a lane,
+// into LDS, where thread e adds expert e's in order.
+constexpr int kRouterLds = 65536;
+constexpr int router_round(int npad) { return kRouterLds / 4 / npad; }
+template <int EPL>
+__global__ __launch_bounds__(256) void router_topk_wide_kernel(const float* __restrict__ part, int n,
+                                                               int npad, int ks, int k,
+                                                               float* __restrict__ logits,
+                                                               int32_t* __restrict__ ids,
+                                                               float* __restrict__ w) {
+    constexpr int PER = kRouterLds / 16 / 256;   // 16-byte loads of a thread and round
+    extern __shared__ __attribute__((aligned(16))) float sl[];
+    const int tid = threadIdx.x, lane = tid & 63, round = router_round(npad);
+    const int64_t t = blockIdx.x;
+    float v = 0.0f;
+    for (int s0 = 0; s0 < ks; s0 += round) {
+        const int rows = ks - s0 < round ? ks - s0 : round, quads = rows * npad / 4;
+        const floatx4* const p = (const floatx4*)(part + (t * ks + s0) * npad);
+        floatx4 q[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (tid + 256 * j < quads) q[j] = p[tid + 256 * j];
+        if (s0) __syncthreads();   // the last round's values have been read
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (tid + 256 * j < quads) ((floatx4*)sl)[tid + 256 * j] = q[j];
+        __syncthreads();
+        if (tid < npad) {
+#pragma unroll 16
+            for (int s = 0; s < rows; ++s) v += sl[s * npad + tid];
+        }
+    }
+    if (logits && tid < n) logits[t * n + tid] = v;
+    __syncthreads();   // the sums have been formed
+    if (tid < npad) sl[tid] = v;
+    __syncthreads();
+    if (tid >= 64) return;   // no barrier follows
+    float lv[EPL];
+#pragma unroll
+    for (int q = 0; q < EPL; ++q) lv[q] = lane + 64 * q < npad ? sl[lane + 64 * q] : 0.0f;
+    float p_;
+    const int e = select_token<EPL>(lv, n, k, lane, &p_);
+    if (lane < k) {
+        ids[t * k + lane] = e;
+        w[t * k + lane] = p_;
     }
 }
 
@@ -722,25 +782,33 @@ hipError_t launch_route_paths(const float* logits, const uint64_t* packed, int64
     return hipGetLastError();
 }
 
-// K split of the two-launch router: ks slices of 4 x `steps` 32-wide K steps (a wave's share),
-// about 512 workgroups in all.
+// K split of the two-launch router: slices of `steps` 32-wide K steps, about 2048 waves in all.
 void router_split(int64_t T, int H, int n, int* et, int64_t* tt, int* ks, int* steps) {
     *et = (int)ceil_div(n, 16);
     *tt = ceil_div(T, 16);
     const int KT = H / 32;
-    int64_t want = 512 / ((int64_t)*et * *tt);
-    want = want < 1 ? 1 : (want > kRouterSlices ? kRouterSlices : want);
-    *steps = (int)ceil_div(KT, want * 4);
-    *ks = (int)ceil_div(KT, *steps * 4);
+    const int64_t tiles = (int64_t)*et * *tt;
+    int64_t want = ceil_div(2048, tiles > 0 ? tiles : 1);
+    want = want < 1 ? 1 : (want > KT ? KT : want);
+    *steps = (int)ceil_div(KT, want);
+    *ks = (int)ceil_div(KT, *steps);
 }
 
-// Sized for slices of the K steps that about 2048 waves leave each (never fewer than router_split's).
 size_t router_ws_bytes(int64_t T, int H, int n) {
-    const int64_t et = ceil_div(n, 16), tt = ceil_div(T, 16), KT = H / 32;
-    int64_t want = ceil_div(2048, et * tt > 0 ? et * tt : 1);
-    want = want < 1 ? 1 : (want > KT ? KT : want);
-    const int64_t ks = ceil_div(KT, ceil_div(KT, want));
+    int et, ks, steps;
+    int64_t tt;
+    router_split(T, H, n, &et, &tt, &ks, &steps);
     return align_up((size_t)ks * T * et * 16 * sizeof(float), 256);
+}
+
+template <int EPL>
+void launch_router_topk(const float* part, int64_t T, int n, int npad, int ks, int k, float* logits,
+                        int32_t* ids, float* w, hipStream_t s) {
+    const unsigned grid = (unsigned)T;
+    if (ks * EPL <= 4) router_topk_kernel<EPL, 4 / EPL><<<grid, 64, 0, s>>>(part, n, npad, ks, k, logits, ids, w);
+    else if (ks * EPL <= 16) router_topk_kernel<EPL, 16 / EPL><<<grid, 64, 0, s>>>(part, n, npad, ks, k, logits, ids, w);
+    else router_topk_wide_kernel<EPL><<<grid, 256, (unsigned)(std::min(ks, router_round(npad)) * npad * sizeof(float)), s>>>(
+        part, n, npad, ks, k, logits, ids, w);
 }
 
 template <class C>
@@ -795,14 +863,14 @@ hipError_t launch_router(bool bf16, const void* x, const void* wr, int64_t T, in
     int et, ks, steps;
     int64_t tt;
     router_split(T, H, n, &et, &tt, &ks, &steps);
-    router_part_kernel<<<(unsigned)(et * tt * ks), 256, 0, s>>>(xb, wb, T, H, n, et, tt, steps, part);
+    const unsigned pgrid = (unsigned)ceil_div(et * tt * ks, 4);
+    router_part_kernel<<<(unsigned)ceil_div(et * tt * ks, 4), 256, 0, s>>>(xb, wb, T, H, n, et, tt, ks, steps, part);
     const int npad = et * 16;
-    const unsigned grid = (unsigned)T;
     switch (epl) {
-        case 1: router_topk_kernel<1><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        case 2: router_topk_kernel<2><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        case 3: router_topk_kernel<3><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
-        default: router_topk_kernel<4><<<grid, 64, 0, s>>>(part, T, n, npad, ks, k, logits, ids, w); break;
+        case 1: launch_router_topk<1>(part, T, n, npad, ks, k, logits, ids, w, s); break;
+        case 2: launch_router_topk<2>(part, T, n, npad, ks, k, logits, ids, w, s); break;
+        case 3: launch_router_topk<3>(part, T, n, npad, ks, k, logits, ids, w, s); break;
+        default: launch_router_topk<4>(part, T, n, npad, ks, k, logits, ids, w, s); break;
     }
     return hipGetLastError();
 }

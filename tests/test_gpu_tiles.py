@@ -60,6 +60,32 @@ def test_router_forms(T, H, n, k):
     check_route_logits(x, wr, k, f"T={T} H={H} n={n} k={k}")
 
 
+# The two-launch router adds in one order: chains of `steps` 32-wide K steps (about 2048 waves share the
+# steps), then their sums in ascending order. Each step here holds one non-zero product, an integer below
+# 2^14 times its chain's power of two, so that a chain of up to 2^9 steps is exact and float32 additions
+# of the chains, whose scales differ, give every bit.
+@pytest.mark.parametrize("T,H,n", [(24, 2048, 64), (1, 4096, 8), (17, 7168, 256), (200, 2048, 64), (256, 1088, 33),
+                                   (40, 192, 130), (700, 2048, 64)])
+def test_router_sum_order(T, H, n):
+    say(f"router order T={T} H={H} n={n}")
+    g = torch.Generator().manual_seed(T + H)
+    KT = H // 32
+    want = min(max(-(-2048 // (-(-n // 16) * -(-T // 16))), 1), KT)
+    steps = -(-KT // want)
+    wr = torch.randint(-127, 128, (n, H), generator=g).float()
+    at = torch.arange(KT) * 32 + torch.randint(0, 32, (T, KT), generator=g)
+    scale = 2.0 ** -torch.randint(0, 24, (T, KT), generator=g)[:, torch.arange(KT) // steps * steps].float()
+    v = torch.randint(-127, 128, (T, KT), generator=g).float() * scale
+    x = torch.zeros((T, H)).scatter_(1, at, v)
+    lg = pcm.pcm_route_logits(x.to(DEV, torch.bfloat16), wr.to(DEV, torch.bfloat16), 1, want_logits=True)[2]
+    torch.cuda.synchronize()
+    prod = v.numpy()[:, :, None] * wr.numpy().T[at.numpy()]     # [T, KT, n]
+    ref = np.zeros((T, n), np.float32)
+    for s in range(0, KT, steps):
+        ref += prod[:, s:s + steps].sum(1, dtype=np.float32)    # exact in any order
+    assert (lg.cpu().numpy() == ref).all(), int((lg.cpu().numpy() != ref).sum())
+
+
 # The one-launch router folds its sums every few K slices, so its rounding error against 64 bits stays at
 # that of the two launches, which add partial sums of K slices (chains of 51 MFMA steps at H 6528, 1000
 # tokens: error about sqrt(51 / 2); folded, chains of 14 steps and 15 of them, sqrt(14 / 2 + 15 / 2); one
