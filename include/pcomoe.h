@@ -312,11 +312,11 @@ pcm_status pcm_project_combine_scored(pcm_dtype dtype, const void* u, const void
 /* ---------------------------------------------------------------- tests and measurement
  * A layer never needs these. The *_tuned calls are the calls above with a pcm_tuning that
  * forces kernel choices the library otherwise makes by shape (every choice computes the same
- * bits, but for the splits of K: the large tiles' projection slices, and the streaming kernel's
- * default ring, which adds four partial sums where rows are few and K is long) and that records
- * HIP events between the internal stages of a call; tuning = NULL is the plain call. They let
- * tests check each kernel on the same inputs and let benchmarks time each stage on the stream it
- * runs on. Values outside the documented sets give PCM_ERR_ARG. */
+ * bits, but for the large tiles' projection, which adds two partial sums where its tiles would
+ * fill less than the chip and K is long) and that records HIP events between the internal stages
+ * of a call; tuning = NULL is the plain call. They let tests check each kernel on the same inputs
+ * and let benchmarks time each stage on the stream it runs on. Values outside the documented sets
+ * give PCM_ERR_ARG. */
 typedef struct pcm_tuning {
     int tile;              /* 0: chosen by the shape (smaller tiles of 64 rows among the choices); 'S' the few-row
                               streaming kernel, 'M' the medium tiles, 'L' the large tiles on four waves,

@@ -38,7 +38,7 @@
 //    load covering whole 128-byte lines; the weights are the traffic. A register-ring
 //    variant (fragments loaded straight into registers several k-steps ahead) runs where
 //    the ring's 32-bit offsets would not reach. Where K is long, the four waves of a workgroup
-//    split it over the same weight rows (LStream).
+//    share its slices over the same weight rows (LStream).
 //  * "ring" (gemm_ring.h: 64 x 128 and 64 x 64 tiles, several workgroups on a compute unit): few
 //    rows per group, and products whose large tiles would leave most of the chip idle.
 // The MFMA takes the weight fragment as its first operand, so each lane's four
@@ -895,22 +895,34 @@ __global__ __launch_bounds__(SWAVES * 64) void gemm_stream_kernel(GemmArgs g, in
 // entry points require of H and F), and `a` and one group's weights are below 4 GiB (32-bit
 // buffer offsets); otherwise the register-ring kernel runs.
 //
-// KW = 1: the four waves own NB * 16 weight rows each. KW = 4: they own the same NB * 16 rows and
-// take every fourth slice of K, adding their sums through LDS in wave order: four times the
-// workgroups where the weight rows alone would leave compute units idle or too little in flight.
+// KW = 1: the four waves own NB * 16 weight rows each. KW = 4: the workgroup owns NB * 16 rows; each
+// wave loads every fourth slice of K into its own slots and runs some of the output blocks over all
+// slices, in ascending order, so the sums are those of every other kernel, bit for bit. Four times
+// the workgroups, where the weight rows alone would leave compute units idle or too little in
+// flight. One barrier per G slices: it says that their loads have landed and that the slots of the G
+// before them, which are then reloaded, have been read; 4 D - G slices are in flight between two.
 // (The body is a device function: the buffer resources and LDS-destination loads it uses have
 // no host form, and the host pass does not emit a kernel whose own body uses them.)
-template <int MODE, int NB, int MB, int D, int KW>
+template <int MODE, int NB, int MB, int D, int KW, int G>
 struct LStream {
     static constexpr int kWaveCols = (MODE == kExpand) ? NB * 8 : NB * 16;   // output columns
     static constexpr int kWgCols = kWaveCols * (KW == 1 ? SWAVES : 1);
     static constexpr int kSlot = (NB + MB) * 2048;   // NB weight blocks, then MB activation blocks
     static constexpr int kLds = SWAVES * D * kSlot;
     static constexpr int kLoads = 2 * (NB + MB);     // loads of a slice
-    static_assert(KW == 1 || KW == SWAVES, "the waves share their rows or their slices");
+    static constexpr int kUnits = (MODE == kExpand ? NB / 2 : NB) * MB;   // blocks of 16 x 16 outputs
+    static constexpr int U = KW == 1 ? kUnits : (kUnits + SWAVES - 1) / SWAVES;   // of them in a wave
+    static constexpr int kSteady = G == SWAVES ? D - 2 : D - 1;   // KW = 4: slices that may be in flight behind the one waited for
+    static_assert(KW == 1 || (KW == SWAVES && (G == 2 || (G == SWAVES && D > 2))), "the waves share their rows or their slices");
     static_assert((MODE != kExpand || NB % 2 == 0) && D >= 2 && (D - 1) * kLoads <= 62, "gate/up halves; vmcnt range");
-    static_assert(KW == 1 || SWAVES * NB * MB * 1024 <= kLds, "the waves' sums fit the ring");
 };
+
+// Waits until at most n * LOADS of the wave's loads are in flight, for n = 0 .. MOST (no wait otherwise).
+template <int LOADS, int MOST>
+__device__ __forceinline__ void wait_last(int n) {
+    if (n == MOST) __builtin_amdgcn_s_waitcnt(waitcnt_imm(MOST * LOADS, kNoLgkm));
+    if constexpr (MOST > 0) wait_last<LOADS, MOST - 1>(n);
+}
 
 // One output row r and 4 columns from c on: the projection's store or accumulation.
 template <int MODE>
@@ -932,10 +944,10 @@ __device__ inline void store_swiglu4(const GemmArgs& g, int r, int c, const floa
 }
 
 // Rows [row0, row1) of group e (at most 16 * MB), N tile ntile.
-template <int MODE, int NB, int MB, int D, int KW, bool NT>
+template <int MODE, int NB, int MB, int D, int KW, int G, bool NT>
 __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e, int row0, int row1,
                                              int ntile) {
-    using C = LStream<MODE, NB, MB, D, KW>;
+    using C = LStream<MODE, NB, MB, D, KW, G>;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int K = g.K, N = g.N;
     const int col0 = KW == 1 ? (ntile * SWAVES + wave) * C::kWaveCols : ntile * C::kWaveCols;
@@ -945,17 +957,21 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
     // source rows of the activation loads, (the projection) the row scales: loaded first, and used
     // only once the first weights are on their way too
     int arow[MB][2];
-    float sc[MB];
+    constexpr int kScales = KW == 1 ? MB : C::U;
+    float sc[kScales];   // of row block m, or (KW = 4) of the row block of this wave's block u
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             arow[m][h] = min(row0 + m * 16 + h * 8 + (lane >> 3), row1 - 1);
             if (g.gather) arow[m][h] = g.gather[arow[m][h]];
         }
-        sc[m] = 1.0f;
+#pragma unroll
+    for (int u = 0; u < kScales; ++u) {
+        sc[u] = 1.0f;
+        const int m = KW == 1 ? u : (u * SWAVES + wave) % MB;
         if constexpr (MODE != kExpand)
-            if (g.row_scale) sc[m] = g.row_scale[scale_row(g, min(row0 + m * 16 + r16, row1 - 1))];
+            if (g.row_scale) sc[u] = g.row_scale[scale_row(g, min(row0 + m * 16 + r16, row1 - 1))];
     }
     // weight row (within expert e) behind row R of block b; rows past N repeat row N - 1
     auto wrow = [&](int b, int R) {
@@ -976,9 +992,10 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
             const int R = h * 8 + (lane >> 3);
             voff[b][h] = (uint32_t)(wrow(b, R) * (int64_t)K * 2 + ((lane & 7) ^ ((R >> 1) & 7)) * 16);
         }
-    // this wave's slices of 64 K values: first, first + KW, ...
-    const int first = KW == 1 ? 0 : wave;
-    const int KP = (K / 64 - first + KW - 1) / KW;
+    // this wave loads slices wave, wave + KW, ... (KW = 1: all) of 64 K values
+    const int slices = K / 64, first = KW == 1 ? 0 : wave;
+    const int KP = (slices - first + KW - 1) / KW;   // at least 2 with KW = 4 (K >= 512)
+    // (past the end, in the first slots only: the last slice again, never used)
     auto issue_w = [&](int j, int p) {
         char* slot = ring + j * C::kSlot;
 #pragma unroll
@@ -987,7 +1004,7 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
             for (int h = 0; h < 2; ++h)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds((MODE == kExpand && b >= NB / 2) ? rb1 : rb0,
                                                          (PCM_LDS void*)(slot + b * 2048 + h * 1024), 16,
-                                                         voff[b][h], (first + p * KW) * 128, 0, weight_policy(NT));
+                                                         voff[b][h], (first + min(p, KP - 1) * KW) * 128, 0, weight_policy(NT));
     };
     auto issue_a = [&](int j, int p) {
         char* slot = ring + j * C::kSlot;
@@ -996,13 +1013,18 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (PCM_LDS void*)(slot + (NB + m) * 2048 + h * 1024), 16,
-                                                         aoff[m][h], (first + p * KW) * 128, 0, 0);
+                                                         aoff[m][h], (first + min(p, KP - 1) * KW) * 128, 0, 0);
     };
+    // Issued before the loop: D - 1 slices (KW = 1) or D, every weight load before every activation
+    // load, whose row indices are still on their way, with the rings that grouped rows take
+    constexpr int kAhead = KW == 1 ? D - 1 : D;
+    constexpr bool kWeightsFirst = KW == 1 || D == 2;
+    if constexpr (kWeightsFirst)
 #pragma unroll
-    for (int j = 0; j < D - 1; ++j) issue_w(j, min(j, KP - 1));   // past the end: re-read, never used
+        for (int j = 0; j < kAhead; ++j) issue_w(j, j);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int R = h * 8 + (lane >> 3);
@@ -1010,54 +1032,58 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
             src = src < 0 ? 0 : (src >= g.a_rows ? g.a_rows - 1 : src);
             aoff[m][h] = (uint32_t)(src * K * 2 + ((lane & 7) ^ ((R >> 1) & 7)) * 16);
         }
-        // the scale has landed here (a load into a register still in flight across the loop makes
-        // the compiler wait for every load in it)
-        if constexpr (MODE != kExpand) asm volatile("" : "+v"(sc[m])::"memory");
-    }
+    // the scales have landed here (a load into a register still in flight across the loop makes
+    // the compiler wait for every load in it)
+    if constexpr (MODE != kExpand)
 #pragma unroll
-    for (int j = 0; j < D - 1; ++j) issue_a(j, min(j, KP - 1));
+        for (int u = 0; u < kScales; ++u) asm volatile("" : "+v"(sc[u])::"memory");
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+        if constexpr (!kWeightsFirst) issue_w(j, j);
+        issue_a(j, j);
+    }
     // fragment of row r16, chunk 4 * step + kg
     const int fo0 = r16 * 128 + ((kg ^ ((r16 >> 1) & 7)) * 16);
     const int fo1 = r16 * 128 + (((4 + kg) ^ ((r16 >> 1) & 7)) * 16);
 
-    floatx4 acc[NB][MB];
+    // lane holds output columns c..c+3 (c = 4 * (lane >> 4)) of activation row r16 in each block
+    if constexpr (KW == 1) {
+        floatx4 acc[NB][MB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int m = 0; m < MB; ++m) acc[b][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int base = 0; base < KP; base += D) {
+            for (int m = 0; m < MB; ++m) acc[b][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int base = 0; base < KP; base += D) {
 #pragma unroll
-        for (int j = 0; j < D; ++j) {
-            const int p = base + j;
-            if (p >= KP) break;
-            // slot (j + D - 1) % D held slice p - 1, whose fragments the previous MFMAs used
-            if (p + D - 1 < KP) {
-                issue_w((j + D - 1) % D, p + D - 1);
-                issue_a((j + D - 1) % D, p + D - 1);
-            }
-            // slice p has landed: only loads issued after it may still be in flight (of the first
-            // D - 1 slices every weight load came before every activation load)
-            if (p + D - 1 >= KP) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkm));
-            else if (j < D - 2 && base == 0) __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 2) * 2 * MB + C::kLoads, kNoLgkm));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 1) * C::kLoads, kNoLgkm));
-            const char* slot = ring + j * C::kSlot;
+            for (int j = 0; j < D; ++j) {
+                const int p = base + j;
+                if (p >= KP) break;
+                // slot (j + D - 1) % D held slice p - 1, whose fragments the previous MFMAs used
+                if (p + D - 1 < KP) {
+                    issue_w((j + D - 1) % D, p + D - 1);
+                    issue_a((j + D - 1) % D, p + D - 1);
+                }
+                // slice p has landed: only loads issued after it may still be in flight (of the first
+                // D - 1 slices every weight load came before every activation load)
+                if (p + D - 1 >= KP) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkm));
+                else if (j < D - 2 && base == 0) __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 2) * 2 * MB + C::kLoads, kNoLgkm));
+                else __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 1) * C::kLoads, kNoLgkm));
+                const char* slot = ring + j * C::kSlot;
 #pragma unroll
-            for (int st = 0; st < 2; ++st) {
-                const int fo = st ? fo1 : fo0;
-                typename Frag<MODE>::T av[MB];
+                for (int st = 0; st < 2; ++st) {
+                    const int fo = st ? fo1 : fo0;
+                    typename Frag<MODE>::T av[MB];
 #pragma unroll
-                for (int m = 0; m < MB; ++m) av[m] = Frag<MODE>::acts(slot + (NB + m) * 2048 + fo);
+                    for (int m = 0; m < MB; ++m) av[m] = Frag<MODE>::acts(slot + (NB + m) * 2048 + fo);
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const typename Frag<MODE>::T wv = Frag<MODE>::weights(slot + b * 2048 + fo);
+                    for (int b = 0; b < NB; ++b) {
+                        const typename Frag<MODE>::T wv = Frag<MODE>::weights(slot + b * 2048 + fo);
 #pragma unroll
-                    for (int m = 0; m < MB; ++m) acc[b][m] = mfma_step(wv, av[m], acc[b][m]);
+                        for (int m = 0; m < MB; ++m) acc[b][m] = mfma_step(wv, av[m], acc[b][m]);
+                    }
                 }
             }
         }
-    }
-    // lane holds output columns c..c+3 (c = 4 * (lane >> 4)) of activation row r16 in each block
-    if constexpr (KW == 1) {
 #pragma unroll
         for (int m = 0; m < MB; ++m) {
             const int r = row0 + m * 16 + r16;
@@ -1077,43 +1103,86 @@ __device__ __forceinline__ void lstream_tile(const GemmArgs& g, char* lds, int e
             }
         }
     } else {
-        // every wave's sums into LDS (its ring is free once every wave is past its loop), then
-        // each wave finishes its share of the blocks, adding in wave order
-        __syncthreads();
-        floatx4* const sums = (floatx4*)lds;   // [wave][b][m][lane]
+        constexpr int U = C::U, P = MODE == kExpand ? 2 : 1;
+        floatx4 acc[U][P];   // block i = u * 4 + wave: weight block i / MB (and its up half), row block i % MB
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int m = 0; m < MB; ++m) sums[((wave * NB + b) * MB + m) * 64 + lane] = acc[b][m];
-        __syncthreads();
-        auto total = [&](int b, int m) {
-            floatx4 t = sums[(b * MB + m) * 64 + lane];
+            for (int h = 0; h < P; ++h) acc[u][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto has = [&](int u) { return (u + 1) * SWAVES <= C::kUnits || u * SWAVES + wave < C::kUnits; };
+        // the blocks of this wave over n slices, ascending: slots 0, D, 2 D .. of the waves' rings from `slots` on
+        auto run = [&](const char* slots, auto n) {
 #pragma unroll
-            for (int q = 1; q < SWAVES; ++q) t += sums[((q * NB + b) * MB + m) * 64 + lane];
-            return t;
+            for (int u = 0; u < U; ++u) {
+                if (!has(u)) continue;   // wave-uniform
+                const int b = (u * SWAVES + wave) / MB, m = (u * SWAVES + wave) % MB;
+                // every fragment is read before the first MFMA (a wave has few blocks, and their MFMAs are a
+                // chain: with reads two or three ahead, as the compiler orders them, the chain waited for each)
+                constexpr int N = decltype(n)::value;
+                typename Frag<MODE>::T av[N][2];
+                bf16x8 wv[N][2][P];
+#pragma unroll
+                for (int q = 0; q < N; ++q)
+#pragma unroll
+                    for (int st = 0; st < 2; ++st) {
+                        const char* slot = slots + q * D * C::kSlot + (st ? fo1 : fo0);
+                        av[q][st] = Frag<MODE>::acts(slot + (NB + m) * 2048);
+#pragma unroll
+                        for (int h = 0; h < P; ++h) wv[q][st][h] = *(const bf16x8*)(slot + (b + h * (NB / 2)) * 2048);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < N; ++q)
+#pragma unroll
+                    for (int st = 0; st < 2; ++st)
+#pragma unroll
+                        for (int h = 0; h < P; ++h)
+                            acc[u][h] = mfma_step(Frag<MODE>::wide(wv[q][st][h]), av[q][st], acc[u][h]);
+            }
         };
-        constexpr int kBlocks = (MODE == kExpand ? NB / 2 : NB) * MB;
+        // a round: one slice of every wave; slice r of this wave is in slot j = r % D
+        for (int r = 0, j = 0; r * SWAVES < slices; ++r, j = j + 1 == D ? 0 : j + 1) {
 #pragma unroll
-        for (int i0 = 0; i0 < kBlocks; i0 += SWAVES) {
-            const int i = i0 + wave;
-            if (i >= kBlocks) break;
-            const int b = i / MB, m = i % MB;
-            const int r = row0 + m * 16 + r16, c = col0 + b * 16 + 4 * kg;
-            if (r >= row1 || c >= N) continue;
-            if constexpr (MODE == kExpand) {
-                store_swiglu4(g, r, c, total(b, m), total(b + NB / 2, m));
-            } else {
-                float s = sc[0];
-#pragma unroll
-                for (int q = 1; q < MB; ++q) s = m == q ? sc[q] : s;
-                store_down4<MODE>(g, r, c, total(b, m), s);
+            for (int h = 0; h < SWAVES / G; ++h) {   // slices h * G .. h * G + G - 1 of the round
+                // They have landed: of each wave that owns one, only loads issued after it are in flight,
+                // kSteady slices while there are any left to issue (a wave that owns none of them has no more
+                // than that in flight). Slice 0 with the weights first: the activations of slice 1.
+                if (kWeightsFirst && r == 0) {
+                    __builtin_amdgcn_s_waitcnt(waitcnt_imm((D - 1) * 2 * MB, 0));
+                } else if (r + C::kSteady < KP) {
+                    __builtin_amdgcn_s_waitcnt(waitcnt_imm(C::kSteady * C::kLoads, 0));
+                } else {
+                    __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNoVm, 0));
+                    wait_last<C::kLoads, C::kSteady - 1>(KP - 1 - r);
+                }
+                ring_barrier();
+                // the G slices before these have been read: their waves reload the slots
+                const int done = h ? r : r - 1;
+                if ((G == SWAVES || wave / G != h) && done >= 0 && done + D < KP) {
+                    const int slot = h ? j : (j ? j : D) - 1;
+                    issue_w(slot, done + D);
+                    issue_a(slot, done + D);
+                }
+                const int p = r * SWAVES + h * G;
+                const char* const slots = lds + (h * G * D + j) * C::kSlot;
+                if (p + G <= slices) run(slots, std::integral_constant<int, G>());
+                else
+                    for (int q = 0; p + q < slices; ++q) run(slots + q * D * C::kSlot, std::integral_constant<int, 1>());
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = (u * SWAVES + wave) / MB, m = (u * SWAVES + wave) % MB;
+            const int r = row0 + m * 16 + r16, c = col0 + b * 16 + 4 * kg;
+            if (!has(u) || r >= row1 || c >= N) continue;
+            if constexpr (MODE == kExpand) store_swiglu4(g, r, c, acc[u][0], acc[u][1]);
+            else store_down4<MODE>(g, r, c, acc[u][0], sc[u]);
         }
+    }
 }
 
 // once: weights_once.
-template <int MODE, int NB, int MB, int D, int KW>
+template <int MODE, int NB, int MB, int D, int KW, int G>
 __global__ __launch_bounds__(SWAVES * 64) void gemm_lstream_kernel(GemmArgs g, int64_t mt_upper, int nt,
                                                                   bool once) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -1125,23 +1194,23 @@ __global__ __launch_bounds__(SWAVES * 64) void gemm_lstream_kernel(GemmArgs g, i
     const int ntile = MODE == kExpand ? (int)(blockIdx.x % nt) : (int)(blockIdx.x / mt_upper);
     if (!find_tile<16 * MB>(g.offsets, g.n, g.a_rows, mt, s_tile)) return;
     if (once && s_tile[3] <= 16 * MB)   // the group's only row tile
-        lstream_tile<MODE, NB, MB, D, KW, true>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
+        lstream_tile<MODE, NB, MB, D, KW, G, true>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
     else
-        lstream_tile<MODE, NB, MB, D, KW, false>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
+        lstream_tile<MODE, NB, MB, D, KW, G, false>(g, lds, s_tile[0], s_tile[1], s_tile[2], ntile);
 }
 
-template <int MODE, int NB, int MB, int D, int KW = 1>
+template <int MODE, int NB, int MB, int D, int KW = 1, int G = 1>
 hipError_t launch_lstream_cfg(const GemmArgs& g, int64_t R, hipStream_t s) {
-    using C = LStream<MODE, NB, MB, D, KW>;
+    using C = LStream<MODE, NB, MB, D, KW, G>;
     const int64_t mt_upper = most_tiles(g, R, 16 * MB);
     const int nt = (int)ceil_div(g.N, C::kWgCols);
     const int64_t grid = mt_upper * nt;
     if (grid <= 0) return hipSuccess;
     // set on every launch (idempotent, and the library keeps no state between calls)
-    const hipError_t err = hipFuncSetAttribute((const void*)gemm_lstream_kernel<MODE, NB, MB, D, KW>,
+    const hipError_t err = hipFuncSetAttribute((const void*)gemm_lstream_kernel<MODE, NB, MB, D, KW, G>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, C::kLds);
     if (err != hipSuccess) return err;
-    gemm_lstream_kernel<MODE, NB, MB, D, KW><<<dim3((unsigned)grid), dim3(SWAVES * 64), C::kLds, s>>>(
+    gemm_lstream_kernel<MODE, NB, MB, D, KW, G><<<dim3((unsigned)grid), dim3(SWAVES * 64), C::kLds, s>>>(
         g, mt_upper, nt, weights_once(g, R, MODE));
     return hipGetLastError();
 }
@@ -1166,11 +1235,12 @@ inline bool offsets_reach(const GemmArgs& g) {
     return g.a_rows * g.K * 2 < (int64_t(1) << 32) && (int64_t)g.N * g.K * 2 < (int64_t(1) << 32);
 }
 
-// The streaming kernels that split K over a workgroup's waves (KW = 4). One group of rows: every
+// The streaming kernels whose waves share the slices of K (KW = 4). One group of rows: every
 // output column block has few workgroups (2048 columns: 64 of 32), so each takes up to 64 rows at
-// once, and the projection 16 columns per workgroup. Shared expert, H 2048, F 5632, three kernels,
-// cold weights: 1 row 55.9 -> 20.7 us, 48 rows 85.2 -> 25.8, 64 rows 87.3 -> 27.5 (the large tiles
-// from 16 rows on before, 8 to 44 workgroups).
+// once, and the projection 16 columns per workgroup. Shared expert, H 2048, F 5632, the layer's three
+// kernels: 1 row 55.9 -> 22.1 us, 48 rows 69.6 -> 25.4, 64 rows 87.3 -> 25.7 (the large tiles from 16
+// rows on before, 8 to 44 workgroups). With every wave's own sums over its slices, added at the end,
+// they took 18.9, 23.6 and 23.9, but u and y then differed in their last bits from every other kernel's.
 //
 // 16-column blocks per workgroup: one, or two where one makes more workgroups than there are compute
 // units (the activations are then fetched half as often: 48 rows, H 2048, F 5632, the three kernels
@@ -1188,41 +1258,55 @@ inline int one_group_row_blocks(const GemmArgs& g, int64_t R) {
         if (ceil_div(R, 16 * m) * ceil_div(g.N, 16) <= 256) return m;
     return (int)std::min<int64_t>(4, ceil_div(R, 16));
 }
+// One group of rows: rings of 64 to 80 KB (two workgroups fit a compute unit where there are that many),
+// two slices of each wave where a slice is more than that allows; deeper rings measured slower (up to 144
+// KB: 48 rows, three kernels 26.8 us). A barrier per four slices, per two where two slices of each wave are
+// all the ring holds (H 2048, F 5632, 1 row, projection 21.8 us with a barrier per two slices, 17.8 with
+// one per four).
+template <int MODE, int NB, int MB>
+hipError_t launch_stream_group(const GemmArgs& g, int64_t R, hipStream_t s) {
+    constexpr int D = NB + MB == 2 ? 4 : (NB + MB == 3 ? 3 : 2);
+    return launch_lstream_cfg<MODE, NB, MB, D, SWAVES, (D > 2 ? SWAVES : 2)>(g, R, s);
+}
 template <int MODE>
-hipError_t launch_stream_ksplit(const GemmArgs& g, int64_t R, hipStream_t s) {
+hipError_t launch_stream_shared(const GemmArgs& g, int64_t R, hipStream_t s) {
     if (!g.offsets) {
         constexpr int E = MODE == kExpand ? 2 : 1;   // weight blocks of 16 output columns
         if (one_group_blocks(g, R) == 2) {
-            if (R <= 16) return launch_lstream_cfg<MODE, 2 * E, 1, 3, 4>(g, R, s);
-            if (R <= 32) return launch_lstream_cfg<MODE, 2 * E, 2, 2, 4>(g, R, s);
-            if (R <= 48) return launch_lstream_cfg<MODE, 2 * E, 3, 2, 4>(g, R, s);
-            return launch_lstream_cfg<MODE, 2 * E, 4, 2, 4>(g, R, s);
+            if (R <= 16) return launch_stream_group<MODE, 2 * E, 1>(g, R, s);
+            if (R <= 32) return launch_stream_group<MODE, 2 * E, 2>(g, R, s);
+            if (R <= 48) return launch_stream_group<MODE, 2 * E, 3>(g, R, s);
+            return launch_stream_group<MODE, 2 * E, 4>(g, R, s);
         }
         switch (one_group_row_blocks(g, R)) {
-            case 1: return launch_lstream_cfg<MODE, E, 1, 3, 4>(g, R, s);
-            case 2: return launch_lstream_cfg<MODE, E, 2, 3, 4>(g, R, s);
-            case 3: return launch_lstream_cfg<MODE, E, 3, 2, 4>(g, R, s);
-            default: return launch_lstream_cfg<MODE, E, 4, 2, 4>(g, R, s);
+            case 1: return launch_stream_group<MODE, E, 1>(g, R, s);
+            case 2: return launch_stream_group<MODE, E, 2>(g, R, s);
+            case 3: return launch_stream_group<MODE, E, 3>(g, R, s);
+            default: return launch_stream_group<MODE, E, 4>(g, R, s);
         }
     }
     // 32 rows per tile from a mean of 4 rows on, where groups of more than 16 become common (40
-    // tokens on the Mixtral shape: expansion 339 -> 311 us, projection 210 -> 188; below, 0-2% slower)
-    return R >= 4 * (int64_t)g.n ? launch_lstream_cfg<MODE, 2, 2, 2, 4>(g, R, s)
-                                 : launch_lstream_cfg<MODE, 2, 1, 2, 4>(g, R, s);
+    // tokens on the Mixtral shape: expansion 339 -> 311 us, projection 210 -> 188; below, 0-2% slower).
+    // Two slices of each wave in the ring and a barrier per two slices, so that three workgroups (two of
+    // the 32-row ones) run on a compute unit: decode shape, 32 tokens, layer 2054 us, 2140 with three
+    // slices and a barrier per four; 40 tokens on the Mixtral shape 474 and 539.
+    return R >= 4 * (int64_t)g.n ? launch_lstream_cfg<MODE, 2, 2, 2, SWAVES, 2>(g, R, s)
+                                 : launch_lstream_cfg<MODE, 2, 1, 2, SWAVES, 2>(g, R, s);
 }
 
-// The default of the streaming kernels. Splitting K pays from long sums on: expansions from H =
-// 1024 (24 tokens, OLMoE shape 93.5 -> 89.4 us; 3 tokens, Mixtral shape 160 -> 139), projections
-// from F = 2048 (Mixtral shape, 3 tokens 126 -> 87 us; decode shape 817 -> 796; at F = 1408 34.7
-// -> 37.6), one group of rows from K = 512; with 16 rows per group and more (only when forced) there
-// are workgroups enough. Without the split the sums run in the order of every other kernel.
+// The default of the streaming kernels. Sharing the slices pays from long sums on: expansions from H =
+// 4096 (Mixtral shape, 3 tokens 206 -> 188 us, 60 tokens 360 -> 316; decode shape 1409 and 1413; H 2048,
+// 64 experts, 24 tokens 75 -> 97), projections from F = 2048 (Mixtral shape, 3 tokens 110 -> 96 us, 60
+// tokens 224 -> 189; F 2048 and H 1024, 16 experts, 8 tokens 14.3 -> 11.2; at F = 1408 34.7 -> 37.6), one
+// group of rows from K = 512; with 16 rows per group and more (only when forced) there are workgroups
+// enough.
 // A forced depth of 2-6 runs the four waves side by side with that ring, 0 the register ring.
 template <int MODE>
 hipError_t launch_stream(const GemmArgs& g, int64_t R, hipStream_t s, int depth) {
     if (g.K % 64 == 0 && offsets_reach(g)) {
         const bool few = !g.offsets || R < 16 * (int64_t)g.n;
-        if (depth < 0 && few && g.K >= (g.offsets ? (MODE == kExpand ? 1024 : 2048) : 512))
-            return launch_stream_ksplit<MODE>(g, R, s);
+        if (depth < 0 && few && g.K >= (g.offsets ? (MODE == kExpand ? 4096 : 2048) : 512))
+            return launch_stream_shared<MODE>(g, R, s);
         // ring depth 3 for the expansion and 2 for the projection (decode-shaped layer: 2-6 within
         // 0.5% for the expansion; the projection 3% slower at 3)
         const int dv = depth >= 0 ? depth : (MODE == kExpand ? 3 : 2);
@@ -1347,7 +1431,7 @@ using RingNarrowTail = RCfg<32, 64, 2, 2, 4>;
 
 // The shape that the large tiles' work runs in when no kernel is forced: 'L', or smaller tiles where
 // the large ones would leave most of the chip idle: 'R' RingWide, 'N' RingNarrow, 'S' the streaming
-// kernel with its K split (one group of rows). Every kernel here is bound by the bytes a compute
+// kernel with shared slices (one group of rows). Every kernel here is bound by the bytes a compute
 // unit loads, 54 KB per us whatever the tile (large tiles 64 KB per 64-wide K stage and 1.18 us,
 // RingWide 24 KB and 0.42-0.48 us, RingNarrow 16 KB and 0.26-0.37 us, streaming 10-12 KB and
 // 0.15-0.22 us), so smaller tiles move more bytes per output but spread over more compute units. The
@@ -1358,7 +1442,7 @@ using RingNarrowTail = RCfg<32, 64, 2, 2, 4>;
 // rows on average are bound by their weights, and one 64-row tile wastes least (OLMoE shape, 256
 // tokens: expansion 116 -> 108 us, projection with mix and combine 87 -> 78; where the projection
 // splits K the large tiles are faster, Mixtral shape, 128 tokens 187 against 208 us). Each shape sums K in
-// the large tiles' order, except the streaming kernel's split.
+// the large tiles' order.
 char pick_shape(const GemmArgs& g, int64_t R, bool expand) {
     const double KT = (double)(g.K / g.ksplit) / 64, ne = g.offsets ? (double)(R < g.n ? R : g.n) : 1;
     if (g.offsets && g.ksplit == 1 && R < 40 * ne) return 'R';

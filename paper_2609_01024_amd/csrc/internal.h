@@ -169,13 +169,14 @@ struct GemmArgs {
 };
 
 // Kernel choices of a bf16 GEMM launch that a caller may force (tests and measurement, through
-// the *_tuned entry points). The defaults choose by shape; every choice gives the same bits.
+// the *_tuned entry points). The defaults choose by shape; every choice gives the same bits, but for
+// the large tiles' projection slices (down_ksplit).
 struct GemmTune {
-    char tile = 0;          // 0: by mean rows per group; 'S' streaming, 'M' medium, 'L' large tiles
+    char tile = 0;          // 0: by shape; 'S' streaming, 'M' medium, 'L' large tiles
     int order = -1;         // large tiles: -1 by shape; 0 grouped, 1 longest first, 2 expert-major
     int window = 0;         // expert-major window (0: 8)
     int group_n = 0;        // N tiles per group of the grouped order (0: 4)
-    int stream_depth = -1;  // streaming kernel: -1 by mode; 0 register ring; 2, 3, 4, 6 LDS slots
+    int stream_depth = -1;  // streaming kernel: -1 by shape; 0 register ring; 2, 3, 4, 6 LDS slots
 };
 
 // Number of K slices the projection of R rows uses (1 or 2): split when the output tiles

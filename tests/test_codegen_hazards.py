@@ -207,3 +207,79 @@ def test_inline_mfma_hazards_absent(gemm_asm):
     assert len(kernels) == 10, kernels
     bad = scan(gemm_asm)
     assert bad == [], "\n".join(f"{k[:60]}: {r}: {i}" for k, r, i in bad[:10])
+
+
+# ------------------------------------------------ results of the compiler's own MFMAs
+# Wait states between a 4-pass MFMA (v_mfma_f32_16x16x32) and another instruction's read of its result.
+# The compiler sees to it, but where the accumulators are copied at the merge of two branches it has put
+# the copies of their first registers in front of the wait (an accumulator chain ended by an if / else of
+# MFMAs: every fourth column was stale).
+RESULT_READ = 7
+
+
+def _all_regs(tok):
+    return {(p, r) for p in "va" for r in _regs(tok, p)}
+
+
+def scan_results(asm_text):
+    """(kernel, instruction) for every read of the result of a v_mfma_f32_16x16x32 fewer than RESULT_READ
+    wait states after it (another MFMA's accumulator operand is forwarded), along the listing and along
+    every branch into its target."""
+    bad = set()
+    for kernel, entries in parse(asm_text).items():
+        labels = {e[1]: i for i, e in enumerate(entries) if e[0] == "label"}
+
+        def walk(start, recent, follow):
+            recent = list(recent)   # (wait states ago, registers)
+            spent = 0
+            for e in entries[start:]:
+                if e[0] != "ins":
+                    continue
+                _, op, parts, in_asm, text = e
+                mfma = op.startswith("v_mfma")
+                store = "store" in op or op.startswith("ds_write")
+                reads = set().union(*[_all_regs(t) for t in (parts[1:] if store else parts[2:4 if mfma else None])])
+                if any(reads & regs for _, regs in recent):
+                    bad.add((kernel, text))
+                n = int(parts[1], 0) + 1 if op == "s_nop" else 1
+                recent = [(age + n, regs) for age, regs in recent if age + n < RESULT_READ]
+                if op.startswith("v_mfma_f32_16x16x32") and not in_asm:
+                    recent.append((0, _all_regs(parts[1])))
+                spent += n
+                if op.startswith(("s_branch", "s_cbranch")) and len(parts) > 1 and parts[1] in labels and recent:
+                    if follow:
+                        walk(labels[parts[1]], recent, follow - 1)
+                    if op == "s_branch":
+                        if follow < 4:
+                            return
+                        recent = []
+                if op == "s_endpgm" or (follow < 4 and not recent):
+                    if follow < 4:
+                        return
+                    recent = []
+        walk(0, [], 4)
+    return sorted(bad)
+
+
+def test_result_scanner():
+    """A result copied behind a branch too early is reported, one read after the wait is not."""
+    listing = """_Zk:
+\ts_cbranch_scc1 .LBB0_2
+\tv_mfma_f32_16x16x32_f16 a[8:11], v[2:5], v[8:11], a[4:7]
+\tv_mfma_f32_16x16x32_f16 a[12:15], v[2:5], v[8:11], a[12:15]
+\ts_branch .LBB0_3
+.LBB0_2:
+\tv_accvgpr_mov_b32 a8, a4
+.LBB0_3:
+{gap}\tv_accvgpr_mov_b32 a0, a12
+\ts_nop 7
+\tglobal_store_dwordx4 v[0:1], a[8:11], off
+\ts_endpgm
+"""
+    assert scan_results(listing.format(gap="")) == [("_Zk", "v_accvgpr_mov_b32 a0, a12")]
+    assert scan_results(listing.format(gap="\ts_nop 6\n")) == []
+
+
+def test_mfma_results_waited_for(gemm_asm):
+    bad = scan_results(gemm_asm)
+    assert bad == [], "\n".join(f"{k[:90]}: {i}" for k, i in bad[:10])

@@ -113,7 +113,7 @@ def test_router_fold_error(T, H, n):
 
 
 # one group of rows (the shared expert) on the shapes that pick_shape chooses between: streaming with
-# the K split (rows 1 to 64 per tile, 17 and 33 and 49 start another block; several row tiles where N is small), 64-row ring tiles (row and
+# slices shared by the waves (rows 1 to 64 per tile, 17 and 33 and 49 start another block; several row tiles where N is small), 64-row ring tiles (row and
 # column remainders), large tiles; K = 512 and 448 are the two sides of the split's line
 @pytest.mark.parametrize("T,H,Fs", [(1, 512, 512), (16, 448, 576), (17, 576, 1088), (33, 1024, 640), (49, 1024, 1600),
                                     (64, 2048, 512), (40, 2112, 2176), (64, 2112, 2176), (65, 2048, 512), (128, 1024, 1984), (300, 1024, 2112),
@@ -136,7 +136,7 @@ def test_dense_swiglu_shapes(T, H, Fs):
         assert torch.equal(y, base + y0), "accumulate adds the stored values"
 
 
-# grouped rows: the streaming K split (below 16 rows per expert; 16-row tiles, 32-row from a mean of
+# grouped rows: streaming with slices shared by the waves (below 16 rows per expert; 16-row tiles, 32-row from a mean of
 # 4 on, several tiles in one expert), ring tiles, and a K split of the projection on the ring; the last
 # three: top-8 mixes whose last wave has few columns (path weights are read from lanes past them)
 @pytest.mark.parametrize("T,H,n,F,k,logits", [(1, 1024, 64, 2048, 8, "normal"), (3, 4096, 8, 2112, 2, "normal"),
@@ -163,6 +163,42 @@ def test_layer_shapes(T, H, n, F, k, logits):
     if R_mean(cfg) >= 16:   # no split of K beyond the large tiles' own: the same sums in the same order
         y = run_layer(d, k, tuning=pcm.Tuning(tile="L"))
         assert np.array_equal(y, ys[0]), "the default and the large tiles"
+
+
+# Whatever the default kernels are, every sum over K runs in one order: that of the streaming kernel whose
+# waves keep to themselves and of the register ring. Expansions share slices from H = 4096, projections
+# from F = 2048 (16-row tiles, 32-row from a mean of 4 on; K slices that the four waves share out unevenly).
+@pytest.mark.parametrize("T,H,n,F,k", [(1, 1024, 64, 2048, 8), (3, 4096, 8, 2112, 2), (40, 1088, 8, 2176, 2),
+                                       (24, 2048, 64, 1024, 8), (17, 1152, 12, 2240, 8), (2, 1216, 3, 2048, 1),
+                                       (2, 4160, 3, 2112, 1), (9, 4224, 3, 2048, 2), (17, 4288, 12, 64, 8)])
+def test_streaming_sum_order(T, H, n, F, k):
+    cfg = scaled(CONFIGS["olmoe"], T=T, H=H, n=n, F=F, k=k, logits="normal", name=f"order{T}_{H}")
+    say(f"streaming sum order {cfg.name}")
+    d = dev(make_inputs(cfg, seed=45))
+    y = run_layer(d, k)
+    for depth in (0, 2):
+        assert np.array_equal(y, run_layer(d, k, tuning=pcm.Tuning(tile="S", stream_depth=depth))), depth
+
+
+# The same for one group of rows, by the medium tiles: every row count per tile of one and of two column
+# blocks per workgroup (two from 257 workgroups on: N = 4160; 2112: rows in tiles of 16 to 64), in the expansion (Fs) and in the projection
+# (H), K slices shared out unevenly; the oracle and accumulation too.
+@pytest.mark.parametrize("T", [1, 16, 17, 33, 48, 49, 64])
+@pytest.mark.parametrize("H,Fs", [(512, 4160), (576, 4160), (640, 2112), (2112, 704), (4160, 512), (4160, 704), (704, 832)])
+def test_dense_swiglu_sum_order(T, H, Fs):
+    cfg = scaled(CONFIGS["finegrained_shared"], T=T, H=H, F=64, shared_F=Fs, name=f"dense{T}")
+    say(f"dense sum order T={T} H={H} Fs={Fs}")
+    inp = make_inputs(cfg, seed=46)
+    d = dev(inp)
+    base = torch.randn((T, H), device=DEV)
+    y0 = torch.full((T, H), float("nan"), device=DEV)
+    pcm.pcm_dense_swiglu(d["x"], *d["shared"], y=y0)
+    y = pcm.pcm_dense_swiglu(d["x"], *d["shared"], y=base.clone(), accumulate=True)
+    m = pcm.pcm_dense_swiglu(d["x"], *d["shared"], tuning=pcm.Tuning(tile="M"))
+    torch.cuda.synchronize()
+    assert_y_close(y0.cpu().numpy(), oracle.dense_swiglu(inp.x, inp.s_gate, inp.s_up, inp.s_down), "bf16", cfg.name)
+    assert torch.equal(y, base + y0), "accumulate adds the stored values"
+    assert torch.equal(y0, m), "the default and the medium tiles"
 
 
 def R_mean(cfg):
