@@ -66,14 +66,18 @@ __device__ inline TokenPaths token_paths(const MixMap& m, int64_t t) {
 
 // Weight (a, b) of the token in lane a * K + b of every wave, one load for all of them: read where
 // they are used, under the path bit's branch, up to 64 scalar loads ran one after another (top-8, F
-// 1024: 24 tokens 10.5 -> 9.0 us, 8192 tokens 84 -> 76). The empty asm keeps the load here, where every
-// lane is active: moved under a column bound, the lanes past the last column would not hold their weights.
+// 1024: 24 tokens 10.5 -> 9.0 us, 8192 tokens 84 -> 76). The mixes read it with every lane active: a copy
+// or a reload of the register in a branch on the column would leave out the lanes past the last one. So a
+// wave with any column runs whole, its lanes past the last chunk on that chunk again (the same maximum),
+// and only the stores are bounded. The empty asm keeps the load itself here.
 __device__ inline float lane_weight(const TokenPaths& p) {
     const int l = threadIdx.x & 63;
     float v = p.beta ? (l < p.K * p.K ? p.beta[l] : 0.0f) : 1.0f;
     asm volatile("" : "+v"(v));
     return v;
 }
+// First chunk index of this wave, known to be uniform.
+__device__ inline int wave_first() { return __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u); }
 __device__ inline float path_weight(float wv, const TokenPaths& p, int a, int b) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), a * p.K + b));
 }
@@ -114,9 +118,9 @@ __global__ __launch_bounds__(256) void mix_kernel(const float* __restrict__ u, v
         float mx[kMaxK];
 #pragma unroll
         for (int b = 0; b < kMaxK; ++b) mx[b] = 0.f;
-        for (int c = threadIdx.x * 8; c < F; c += blockDim.x * 8) {
+        for (int c0 = wave_first() * 8; c0 < F; c0 += blockDim.x * 8) {   // uniform
             float zz[kMaxK][8];
-            mix8(u, p, wv, F, c, zz);
+            mix8(u, p, wv, F, min(c0 + (int)(threadIdx.x & 63) * 8, F - 8), zz);
 #pragma unroll
             for (int b = 0; b < kMaxK; ++b)
                 if (b < p.nt)
@@ -149,9 +153,11 @@ __global__ __launch_bounds__(256) void mix_kernel(const float* __restrict__ u, v
         }
     }
     // pass 2 (only pass for float32 layers): store z
-    for (int c = threadIdx.x * 8; c < F; c += blockDim.x * 8) {
+    for (int c0 = wave_first() * 8; c0 < F; c0 += blockDim.x * 8) {   // uniform
+        const int c = c0 + (int)(threadIdx.x & 63) * 8;
         float zz[kMaxK][8];
-        mix8(u, p, wv, F, c, zz);
+        mix8(u, p, wv, F, min(c, F - 8), zz);
+        if (c >= F) continue;
 #pragma unroll
         for (int b = 0; b < kMaxK; ++b) {
             if (b >= p.nt) break;
@@ -197,8 +203,8 @@ __global__ __launch_bounds__(1024) void mix_regs_kernel(const float* __restrict_
         for (int b = 0; b < KK; ++b)
 #pragma unroll
             for (int i = 0; i < CPT; ++i) zz[it][b][i] = 0.f;
-        const int c = (threadIdx.x + it * blockDim.x) * CPT;
-        if (c >= F) continue;
+        if ((wave_first() + it * (int)blockDim.x) * CPT >= F) continue;   // uniform
+        const int c = min((int)(threadIdx.x + it * blockDim.x) * CPT, F - CPT);
         // sources in ascending order, each row's 8 values added to every target it feeds;
         // the loads of all sources are issued before the first multiply-add
         float ua[KK][CPT];

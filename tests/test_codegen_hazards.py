@@ -283,3 +283,41 @@ def test_result_scanner():
 def test_mfma_results_waited_for(gemm_asm):
     bad = scan_results(gemm_asm)
     assert bad == [], "\n".join(f"{k[:90]}: {i}" for k, i in bad[:10])
+
+
+# ------------------------------------------------ lane reads of the mix kernels
+def lanes_read_narrowed(asm_text, name):
+    """(kernel, instruction) for every v_readlane in a kernel whose name has `name` in it that runs between
+    a narrowing of exec and its restoration: a register read from another lane has to hold that lane's value,
+    which a copy or a reload made under the narrower exec does not give it. (Registers written by v_writelane
+    hold spilled scalars: lane writes and reads do not depend on exec.)"""
+    bad = []
+    for kernel, entries in parse(asm_text).items():
+        if name not in kernel:
+            continue
+        spilled = {e[2][1] for e in entries if e[0] == "ins" and e[1].startswith("v_writelane")}
+        saved = set()   # registers that hold an exec to restore
+        for e in entries:
+            if e[0] != "ins":
+                continue
+            _, op, parts, _, text = e
+            if op.endswith("saveexec_b64"):
+                saved.add(parts[1])
+            elif op in ("s_or_b64", "s_mov_b64") and parts[1] == "exec":
+                saved.discard(parts[-1])
+            elif op.startswith("v_readlane") and saved and parts[2] not in spilled:
+                bad.append((kernel, text))
+    return bad
+
+
+def test_mix_reads_lanes_with_every_lane_active(tmp_path):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    out = tmp_path / "mix.s"
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                    "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
+                    os.path.join(CSRC, "mix_combine.hip"), "-o", str(out)], check=True, capture_output=True)
+    asm = out.read_text()
+    assert len(re.findall(r"^_Z\S*mix_\S*kernel\S*:", asm, re.M)) >= 8 and "v_readlane" in asm
+    bad = lanes_read_narrowed(asm, "mix_")
+    assert bad == [], "\n".join(f"{k[:80]}: {i}" for k, i in bad[:10])
