@@ -1248,13 +1248,13 @@ inline bool offsets_reach(const GemmArgs& g) {
 inline int one_group_blocks(const GemmArgs& g, int64_t R) {
     return ceil_div(R, 64) * ceil_div(g.N, 16) > 256 ? 2 : 1;
 }
-// 16-row blocks per workgroup where it takes one column block: the fewest that leave no more
-// workgroups than compute units. A workgroup fetches its rows' activations whole, at most 54 GB/s to
+// 16-row blocks per workgroup: with two column blocks all rows, up to 64; with one the fewest that
+// leave no more workgroups than compute units. A workgroup fetches its rows' activations whole, at most 54 GB/s to
 // a compute unit, so where columns alone leave units idle the rows are split over them too (H 2048,
 // F 5632, the three kernels, cold weights: 32 rows 26.3 -> 23.4 us, 64 rows 33.3 -> 27.5; past 256
 // workgroups, H 3072 and F 8192, the split loses: 64 rows 49.0 -> 53.1).
 inline int one_group_row_blocks(const GemmArgs& g, int64_t R) {
-    for (int m = 1; m < 4; ++m)
+    for (int m = 1; m < 4 && one_group_blocks(g, R) == 1; ++m)
         if (ceil_div(R, 16 * m) * ceil_div(g.N, 16) <= 256) return m;
     return (int)std::min<int64_t>(4, ceil_div(R, 16));
 }
@@ -1272,13 +1272,16 @@ template <int MODE>
 hipError_t launch_stream_shared(const GemmArgs& g, int64_t R, hipStream_t s) {
     if (!g.offsets) {
         constexpr int E = MODE == kExpand ? 2 : 1;   // weight blocks of 16 output columns
+        const int mb = one_group_row_blocks(g, R);
         if (one_group_blocks(g, R) == 2) {
-            if (R <= 16) return launch_stream_group<MODE, 2 * E, 1>(g, R, s);
-            if (R <= 32) return launch_stream_group<MODE, 2 * E, 2>(g, R, s);
-            if (R <= 48) return launch_stream_group<MODE, 2 * E, 3>(g, R, s);
-            return launch_stream_group<MODE, 2 * E, 4>(g, R, s);
+            switch (mb) {
+                case 1: return launch_stream_group<MODE, 2 * E, 1>(g, R, s);
+                case 2: return launch_stream_group<MODE, 2 * E, 2>(g, R, s);
+                case 3: return launch_stream_group<MODE, 2 * E, 3>(g, R, s);
+                default: return launch_stream_group<MODE, 2 * E, 4>(g, R, s);
+            }
         }
-        switch (one_group_row_blocks(g, R)) {
+        switch (mb) {
             case 1: return launch_stream_group<MODE, E, 1>(g, R, s);
             case 2: return launch_stream_group<MODE, E, 2>(g, R, s);
             case 3: return launch_stream_group<MODE, E, 3>(g, R, s);
@@ -1434,11 +1437,11 @@ using RingNarrowTail = RCfg<32, 64, 2, 2, 4>;
 // kernel with shared slices (one group of rows). Every kernel here is bound by the bytes a compute
 // unit loads, 54 KB per us whatever the tile (large tiles 64 KB per 64-wide K stage and 1.18 us,
 // RingWide 24 KB and 0.42-0.48 us, RingNarrow 16 KB and 0.26-0.37 us, streaming 10-12 KB and
-// 0.15-0.22 us), so smaller tiles move more bytes per output but spread over more compute units. The
+// 0.12-0.3 us), so smaller tiles move more bytes per output but spread over more compute units. The
 // times below are those rates over 256 compute units (shared expert, H 2048, F 5632, expansion and
-// projection in us, L / R / N / S: 64 rows 29 49 / 19 45 / 16 34 / 19 11; 256 rows 43 106 / 29 44 /
-// 28 34 / 46 31; 1000 rows 52 102 / 73 45 / 82 48 / 145 102; 4096 rows 147 107 / 271 159 / 398 220 /
-// 563 415). The smaller tiles are taken where they come out a fifth faster. Groups of fewer than 40
+// projection in us, L / R / N / S: 64 rows 29 49 / 19 45 / 16 34 / 15 13; 256 rows 43 106 / 29 44 /
+// 28 34 / 35 22; 1000 rows 52 102 / 73 45 / 82 48 / 129 83; 4096 rows 147 107 / 271 159 / 398 220 /
+// 451 307). The smaller tiles are taken where they come out a fifth faster. Groups of fewer than 40
 // rows on average are bound by their weights, and one 64-row tile wastes least (OLMoE shape, 256
 // tokens: expansion 116 -> 108 us, projection with mix and combine 87 -> 78; where the projection
 // splits K the large tiles are faster, Mixtral shape, 128 tokens 187 against 208 us). Each shape sums K in
@@ -1461,9 +1464,9 @@ char pick_shape(const GemmArgs& g, int64_t R, bool expand) {
     if (wide < best) { best = wide; t = 'R'; }
     if (narrow < best) { best = narrow; t = 'N'; }
     if (!g.offsets && g.K >= 512) {
-        const int mb = R > 48 ? 4 : (R > 32 ? 3 : (R > 16 ? 2 : 1));
-        const int nb = one_group_blocks(g, R);
-        const double stream = KT * up(tiles(16 * mb, 16 * nb)) * (2 * ((expand ? 2 : 1) * nb + mb)) / 54 + 3.5;
+        // the blocks that launch_stream_shared takes; a slice takes its bytes' time, or 0.12 us
+        const int nb = one_group_blocks(g, R), mb = one_group_row_blocks(g, R);
+        const double stream = KT * up(tiles(16 * mb, 16 * nb)) * most(0.12, 2.0 * (half * nb + mb) / 54) + 3.5;
         if (stream < best) t = 'S';
     }
     return t;
