@@ -190,6 +190,9 @@ hipError_t launch_ring(const GemmArgs& g, int64_t R, hipStream_t s, int window) 
     const int nt = (int)ceil_div(g.N, MODE == kExpand ? C::BN / 2 : C::BN);
     const int64_t grid = ceil_div(mt_upper * nt * g.ksplit, 8) * 8;
     if (grid <= 0) return hipSuccess;
+    // em_item counts in 32 bits, up to 8 times the items. (No call that fits the card comes near: as many
+    // tiles of at least 32 x 32 outputs are 550 GB of output, or, as tails, 2 TB of weights.)
+    if (grid >= int64_t(1) << 27) return hipErrorInvalidValue;
     // set on every launch (idempotent, and the library keeps no state between calls)
     const hipError_t err = hipFuncSetAttribute((const void*)gemm_ring_kernel<E, C, CT, MODE>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
