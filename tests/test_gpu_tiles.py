@@ -205,6 +205,25 @@ def R_mean(cfg):
     return cfg.T * cfg.k // cfg.n
 
 
+# Weights of more than half of the 256 MB MALL are read non-temporally by the groups of a single row tile:
+# the large tiles on four and eight waves and the 64-row ring tiles (means of 20, 50 and 100 rows; skewed,
+# with groups of one and of several row tiles in a call). One order of the sums (F / 2 is no multiple of 64,
+# so the projection takes one slice of K).
+@pytest.mark.parametrize("T,logits", [(80, "normal"), (200, "zipf"), (400, "normal")])
+def test_nontemporal_weights(T, logits):
+    H, n, F, k = 2048, 8, 4160, 2
+    assert 2 * n * F * H * 2 > 128 << 20 and n * F * H * 2 > 128 << 20   # gate and up, down
+    cfg = scaled(CONFIGS["mixtral"], T=T, H=H, n=n, F=F, k=k, logits=logits, zipf_s=1.1, name=f"nt{T}")
+    say(f"non-temporal weights {cfg.name}")
+    inp = make_inputs(cfg, seed=47)
+    d = dev(inp)
+    y = run_layer(d, k)
+    assert_y_close(y, oracle.layer_inputs(inp), "bf16", cfg.name)
+    for tile in ("S", "M", "L", "W"):
+        say(f"tile {tile}")
+        assert np.array_equal(y, run_layer(d, k, tuning=pcm.Tuning(tile=tile))), tile
+
+
 # path build of up to 256 tokens: one thread per (token, slot), at most two each
 @pytest.mark.parametrize("beta_mode", [0, 1, 2])
 @pytest.mark.parametrize("T,n,k", [(1, 8, 8), (128, 256, 8), (129, 9, 8), (255, 64, 5), (256, 256, 8), (200, 1, 1)])
