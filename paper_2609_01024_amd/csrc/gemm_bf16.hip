@@ -1383,8 +1383,9 @@ hipError_t launch_cfg(const GemmArgs& g, int64_t R, hipStream_t s, const GemmTun
     return hipGetLastError();
 }
 
-// Tile shape: a forced choice (tile = 'S', 'M' or 'L', for tests and tuning), otherwise by the
-// mean rows per group (below 16 the streaming kernel, else the large tiles). The large tiles
+// Tile family: a forced choice (tile = 'S', 'M', 'L' or 'W', for tests and tuning), otherwise by the
+// mean rows per group (below 16 the streaming kernel, else the large tiles, in whose place pick_shape
+// may then take smaller ones). The large tiles
 // address `a` and one group's weights through 32-bit buffer offsets, so both must stay below
 // 4 GiB (a_bytes: all rows of `a`; w_bytes: one group's weights).
 char pick_tile(int64_t R, int groups, int64_t a_bytes, int64_t w_bytes, char tile) {
@@ -1394,8 +1395,8 @@ char pick_tile(int64_t R, int groups, int64_t a_bytes, int64_t w_bytes, char til
     // below 16 rows per group the streaming kernel (weights streamed once, little MFMA work
     // wasted on padding); from 16 on the large tiles, which were faster than the medium ones
     // at every size measured (Mixtral-shaped, 1024 tokens: 2.6 -> 0.87 ms for the two GEMMs
-    // and the combine) and than the streaming kernel from 16 rows per group on; the medium
-    // tiles only where the large tiles' 32-bit offsets would not reach
+    // and the combine) and, of grouped rows, than the streaming kernel; the medium tiles only
+    // where the large tiles' 32-bit offsets would not reach
     const int64_t mean = R / (groups > 0 ? groups : 1);
     if (mean < 16) return 'S';
     return large_ok ? 'L' : 'M';

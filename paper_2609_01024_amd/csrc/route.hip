@@ -481,12 +481,12 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
 // router computes from h): logits[t, e] = x_t . W_r[e], float32 accumulation, on the matrix
 // cores (v_mfma_f32_16x16x32_bf16, router rows as the first operand). The sums over K slices
 // run in a fixed order (deterministic). Two forms (launch_router has the rule):
-//  * router_fused_kernel, one launch: a workgroup owns 32 tokens and every expert. Its first waves run the ring of gemm_ring.h over the 128-byte K slices of the tokens'
-//    and the experts' rows (4 to 12 slices in LDS, so that most of a compute unit's 64 bytes per
-//    clock stay requested), the logits go through LDS, and sixteen waves run the top-k of two
-//    tokens each. x is read once; the router weights come from L2. 8192 tokens, H 2048, 64
-//    experts: 39.0 -> 14.5 us (13.4 without the folds); 16384 tokens, H 7168, 256 experts, without
-//    the folds: 830 -> 158 us.
+//  * router_fused_kernel, one launch: a workgroup owns 32 tokens and every expert. Its first four
+//    waves run the ring of gemm_ring.h over the 128-byte K slices of the tokens' and the experts'
+//    rows (4 to 12 slices in LDS, so that most of a compute unit's 64 bytes per clock stay
+//    requested), the logits go through LDS, and sixteen waves run the top-k of two tokens each. x is
+//    read once; the router weights come from L2. Against the two launches: 8192 tokens, H 2048, 64
+//    experts 35.6 -> 14.4 us (13.4 without the folds); 16384 tokens, H 7168, 256 experts 800 -> 152.
 //  * router_part_kernel, then router_topk_kernel: a wave computes one 16-expert x 16-token block of
 //    partial dot products over one K slice (router_split: about 2048 waves share the work, so that a
 //    few tokens still use many compute units), fragments loaded straight from global memory;
@@ -832,10 +832,14 @@ hipError_t launch_router_fused(const uint16_t* x, const uint16_t* wr, int64_t T,
 // Whether the one-launch router is the faster one. Its workgroups take the bytes of 32 tokens and
 // of every expert (in 64s) at about 65 GB/s each, one workgroup on each of 256 compute units at a
 // time; the two launches move 32 rows per 16 x 16 block at about 9 TB/s in all, 138 times as much
-// (both with 5-6 us besides; without the folds, which add up to 8%, H 2048, 64 experts: 1024 tokens 11.2 against 9.4 us, 2048 tokens 11.5
-// against 13.4, 8192 tokens 13.4 against 36.6; H 7168, 256 experts: 1024 tokens 65.6 against 56.4,
-// 2048 tokens 65.9 against 105). With at most 32 experts half of its expert rows would be padding
-// (8 experts, H 4096, 8192 tokens: 21.3 against 19.4 us).
+// (both with 5-6 us besides). Measured on both sides of the line (tokens where it lies: one launch and
+// two, us): H 2048, 64 experts (1657) 1500 13.5 13.2, 1700 13.4 14.7; H 512, 64 experts (1657) 1500 7.6
+// 7.9, 1700 7.6 8.1; H 7168, 256 experts (1243) 1000 69.0 56.8, 1300 69.1 81.2; H 2048, 180 experts
+// (1289) 1000 21.4 21.6, 1300 21.4 22.1; H 4096, 40 experts (2209) 2100 20.1 19.3, 2400 20.1 22.1; H
+// 4096, 128 experts (1381) 1000 25.5 24.1, 1300 25.6 28.3: the times cross at 107 to 140 times as much,
+// and the line is at the upper end, where the order of the sums changes for the fewest calls. With at
+// most 32 experts half of its expert rows would be padding (8 experts, H 4096, 8192 tokens: 21.3 against
+// 19.4 us).
 bool router_fused(int64_t T, int H, int n) {
     if (n <= 32) return false;
     const int64_t row = (int64_t)H * 2, rounds = ceil_div(ceil_div(T, kRouterTok), 256);
@@ -863,7 +867,6 @@ hipError_t launch_router(bool bf16, const void* x, const void* wr, int64_t T, in
     int et, ks, steps;
     int64_t tt;
     router_split(T, H, n, &et, &tt, &ks, &steps);
-    const unsigned pgrid = (unsigned)ceil_div(et * tt * ks, 4);
     router_part_kernel<<<(unsigned)ceil_div(et * tt * ks, 4), 256, 0, s>>>(xb, wb, T, H, n, et, tt, ks, steps, part);
     const int npad = et * 16;
     switch (epl) {
